@@ -15,10 +15,10 @@
 //                   registers (1024 threads x 4 or 6 chunks, or 512 x 8 when
 //                   there are many slices): a cheap lower
 //                   bound of the KMAX-th best value leaves a few candidates,
-//                   ranked by counting (details below).
-//   k_topk_scalar   rows that are not 16-byte aligned: one wave per (row,
-//                   slice) with element loads; each lane keeps a sorted list
-//                   of its KMAX best keys in registers.
+//                   ranked by counting (details below).  Rows may start at
+//                   any element address: the few elements before the slice's
+//                   first 16-byte boundary and after its last whole chunk are
+//                   read one per lane.
 // Sorted lists are merged by a butterfly of 6 steps per wave, each merging two
 // sorted lists with a bitonic network.
 //   k_topk_merge    one workgroup per row ranks the slice results by counting
@@ -146,8 +146,9 @@ __device__ __forceinline__ void store_part(uint64_t* part, int item, int kmax, i
 //   3. Chunks whose image reaches tau are copied with their index to a list
 //      in LDS, then the workgroup examines the listed chunks a thread per
 //      element and appends the elements that reach tau to a candidate list.
-//      The slice's last partial chunk (fewer than one chunk of elements) is
-//      read with plain loads and checked the same way.
+//      The edges of the slice (the elements before its first 16-byte
+//      boundary and after its last whole chunk, fewer than two chunks) are
+//      read with plain loads, one per lane, and checked the same way.
 //   4. The candidates are ranked by counting: the list is cut into parts,
 //      each thread counts the keys of one part above one candidate, and the
 //      counts are summed in LDS.  The candidates of rank below k are the
@@ -267,16 +268,24 @@ k_topk_row(const void* __restrict__ logits, int V, long long ld, int slices, int
   const int v0 = s * slice_len;
   const int v1 = min(V, v0 + slice_len);
   const char* rb = static_cast<const char*>(logits) + static_cast<size_t>(row) * ld * ES;
-  const char* sb = rb + static_cast<size_t>(v0) * ES;  // the slice, 16-byte aligned
-  const int nfull = (v1 - v0) / E;  // whole chunks of the slice (at most NT * NL)
-  const int vt = v0 + nfull * E + tid;  // the last partial chunk, one element per lane
+  const char* sb = rb + static_cast<size_t>(v0) * ES;
+  // elements before the slice's first 16-byte boundary (0 for aligned rows).
+  // Rows of an odd length, or a view, start anywhere; the chunks stay aligned
+  // loads and only the edges are read by element (65 rows x 32003 bf16: a
+  // wave per row reading elements, as such rows did before, 98 us; now 8.1,
+  // the host call)
+  const int head = min(v1 - v0, static_cast<int>((0u - static_cast<uint32_t>(reinterpret_cast<uintptr_t>(sb))) & 15u) / ES);
+  const int vb = v0 + head;         // first element of chunk 0
+  const int nfull = (v1 - vb) / E;  // whole chunks of the slice (at most NT * NL)
+  // the edge elements, one per lane: the head, then the last partial chunk
+  const int vt = tid < head ? v0 + tid : vb + nfull * E + (tid - head);
   const bool tail = vt < v1;
 
   // Chunk u of a lane is u * NT + tid (past the end: the slice's
   // last chunk, never examined); all loads are issued before any wait.
   uint4 cw[NL];
   if (nfull > 0) {
-    const uint4* src = reinterpret_cast<const uint4*>(sb);
+    const uint4* src = reinterpret_cast<const uint4*>(sb + head * ES);
 #pragma unroll
     for (int u = 0; u < NL; ++u) cw[u] = src[min(u * NT + tid, nfull - 1)];
   } else {
@@ -356,7 +365,7 @@ k_topk_row(const void* __restrict__ logits, int V, long long ld, int slices, int
         const int c = s_list[i], e = tid & (E - 1);
         const uint32_t bits = BF16 ? static_cast<uint32_t>(reinterpret_cast<const uint16_t*>(s_ldata + i)[e]) << 16
                                    : reinterpret_cast<const uint32_t*>(s_ldata + i)[e];
-        if (elem_img<BF16>(bits) >= tc) append(bits, v0 + c * E + e);
+        if (elem_img<BF16>(bits) >= tc) append(bits, vb + c * E + e);
       }
     }
   }
@@ -407,7 +416,7 @@ k_topk_row(const void* __restrict__ logits, int V, long long ld, int slices, int
   for (int u = 0; u < NL; ++u) {
     const int c = u * NT + tid;
     if (c < nfull) {
-      const int v = v0 + c * E;
+      const int v = vb + c * E;
 #pragma unroll
       for (int e = 0; e < E; ++e) {
         const uint32_t bits = chunk_bits<BF16>(cw[u], e);
@@ -438,35 +447,6 @@ k_topk_row(const void* __restrict__ logits, int V, long long ld, int slices, int
   for (int r = 0; r < KMAX; ++r) mine = (lane == r) ? l[r] : mine;
   if (slices == 1) emit<BF16>(mine, lane, k, V, rb, row, argmax, topk_idx, topk_val);
   else if (lane < KMAX) store_part<BF16>(part, blockIdx.x, KMAX, lane, mine, rb);
-}
-
-// Rows that are not 16-byte aligned: one wave per (row, slice), element loads.
-template <int KMAX, bool BF16>
-__global__ void __launch_bounds__(kThreads)
-k_topk_scalar(const void* __restrict__ logits, int R, int V, long long ld, int slices,
-              int slice_len, int k, int32_t* __restrict__ argmax, int32_t* __restrict__ topk_idx,
-              float* __restrict__ topk_val, uint64_t* __restrict__ part) {
-  const int lane = threadIdx.x & 63;
-  const int item = blockIdx.x * (kThreads / PTD_WAVE) + (threadIdx.x >> 6);
-  if (item >= R * slices) return;  // whole wave
-  const int row = item / slices, s = item % slices;
-  const int v0 = s * slice_len;
-  const int v1 = min(V, v0 + slice_len);
-  const void* rb = BF16 ? static_cast<const void*>(static_cast<const uint16_t*>(logits) + row * ld)
-                        : static_cast<const void*>(static_cast<const float*>(logits) + row * ld);
-  uint64_t l[KMAX];
-#pragma unroll
-  for (int j = 0; j < KMAX; ++j) l[j] = 0;
-  for (int v = v0 + lane; v < v1; v += PTD_WAVE) {
-    const uint64_t key = make_key(elem_bits<BF16>(rb, v), static_cast<uint32_t>(v));
-    if (key > l[KMAX - 1]) insert<KMAX>(l, key);
-  }
-  wave_merge<KMAX>(l);
-  uint64_t mine = 0;
-#pragma unroll
-  for (int r = 0; r < KMAX; ++r) mine = (lane == r) ? l[r] : mine;
-  if (slices == 1) emit<BF16>(mine, lane, k, V, rb, row, argmax, topk_idx, topk_val);
-  else if (lane < KMAX) store_part<BF16>(part, item, KMAX, lane, mine, rb);
 }
 
 // One workgroup per row: the row's slices * KMAX (key, bits) pairs are ranked
@@ -532,7 +512,6 @@ k_topk_merge(const void* __restrict__ logits, int V, long long ld, int slices, i
 struct TopkPlan {
   int kmax, slices, slice_len;
   int nt, nl;  // k_topk_row: threads per workgroup, 16-byte chunks per lane
-  bool vec;  // 16-byte aligned rows: k_topk_row, else k_topk_scalar
   size_t ws_bytes;
 };
 
@@ -556,10 +535,9 @@ void topk_shape(int R, int V, int E, int* nt, int* nl) {
   }
 }
 
-bool make_topk_plan(int R, int V, int k, int elem_bytes, bool vec, TopkPlan* p) {
+bool make_topk_plan(int R, int V, int k, int elem_bytes, TopkPlan* p) {
   if (R < 1 || V < 1 || k < 1 || k > PTD_MAX_K || k > V) return false;
   p->kmax = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : k <= 8 ? 8 : 16;
-  p->vec = vec;
   const int E = 16 / elem_bytes;
   topk_shape(R, V, E, &p->nt, &p->nl);
   // A slice is at most nt * nl whole chunks (plus, for the last, a partial
@@ -567,7 +545,7 @@ bool make_topk_plan(int R, int V, int k, int elem_bytes, bool vec, TopkPlan* p) 
   const long long max_len = static_cast<long long>(p->nt) * p->nl * E;
   int s = static_cast<int>((V + max_len - 1) / max_len);
   int len = (V + s - 1) / s;
-  len = (len + 7) & ~7;  // keep slice starts 16-byte aligned
+  len = (len + 7) & ~7;  // slices of an aligned row start 16-byte aligned
   s = (V + len - 1) / len;
   if (static_cast<long long>(R) * s > (1LL << 30)) return false;
   p->slices = s;
@@ -579,18 +557,12 @@ bool make_topk_plan(int R, int V, int k, int elem_bytes, bool vec, TopkPlan* p) 
 template <int KMAX, bool BF16>
 void launch(const TopkPlan& pl, const void* logits, int R, int V, long long ld, int k,
             int32_t* am, int32_t* ti, float* tv, uint64_t* part, hipStream_t st) {
-  constexpr int WPB = kThreads / PTD_WAVE;
-  if (pl.vec) {
 #define PTD_TOPK_ROW(nt_, nl_)                                                                   \
   if (pl.nt == nt_ && pl.nl == nl_)                                                              \
     hipLaunchKernelGGL((k_topk_row<KMAX, BF16, nt_, nl_>), dim3(R * pl.slices), dim3(nt_), 0, st, \
                        logits, V, ld, pl.slices, pl.slice_len, k, am, ti, tv, part);
-    PTD_TOPK_ROW(1024, 4) PTD_TOPK_ROW(1024, 6) PTD_TOPK_ROW(512, 8)
+  PTD_TOPK_ROW(1024, 4) PTD_TOPK_ROW(1024, 6) PTD_TOPK_ROW(512, 8)
 #undef PTD_TOPK_ROW
-  } else
-    hipLaunchKernelGGL((k_topk_scalar<KMAX, BF16>), dim3((R * pl.slices + WPB - 1) / WPB),
-                       dim3(kThreads), 0, st, logits, R, V, ld, pl.slices, pl.slice_len, k, am,
-                       ti, tv, part);
   if (pl.slices > 1)
     hipLaunchKernelGGL((k_topk_merge<KMAX, BF16>), dim3(R), dim3(kThreads), 0, st, logits, V, ld,
                        pl.slices, k, part, am, ti, tv);
@@ -613,7 +585,7 @@ void dispatch(const TopkPlan& pl, const void* logits, int R, int V, long long ld
 extern "C" size_t ptd_topk_workspace_bytes(int32_t R, int32_t V, int32_t k) {
   // the dtype is not known here: size for the larger of the bf16 and fp32 plans
   TopkPlan p2, p4;
-  if (!make_topk_plan(R, V, k, 2, true, &p2) || !make_topk_plan(R, V, k, 4, true, &p4)) return 0;
+  if (!make_topk_plan(R, V, k, 2, &p2) || !make_topk_plan(R, V, k, 4, &p4)) return 0;
   return p2.ws_bytes > p4.ws_bytes ? p2.ws_bytes : p4.ws_bytes;
 }
 
@@ -626,9 +598,8 @@ extern "C" int ptd_topk_argmax(const void* logits, ptd_dtype dtype, int32_t R, i
   PTD_RETURN_IF(ld < V, PTD_ERR_SHAPE);
   const size_t es = dtype == PTD_BF16 ? 2 : 4;
   PTD_RETURN_IF(!ptd_aligned(logits, es), PTD_ERR_ALIGN);
-  const bool vec = ptd_aligned(logits, 16) && (static_cast<size_t>(ld) * es) % 16 == 0;
   TopkPlan pl;
-  PTD_RETURN_IF(!make_topk_plan(R, V, k, static_cast<int>(es), vec, &pl), PTD_ERR_SHAPE);
+  PTD_RETURN_IF(!make_topk_plan(R, V, k, static_cast<int>(es), &pl), PTD_ERR_SHAPE);
   if (pl.ws_bytes) {
     PTD_RETURN_IF(!workspace || workspace_bytes < pl.ws_bytes, PTD_ERR_WORKSPACE);
     PTD_RETURN_IF(!ptd_aligned(workspace, 8), PTD_ERR_ALIGN);

@@ -104,7 +104,7 @@ def test_topk_all_equal_and_strided(P):
     rng = np.random.default_rng(1)
     x = W.f32_to_bf16_bits(rng.standard_normal((9, 3001), dtype=np.float32))
     _topk_case(P, x, 6, ld=3008)   # 16-byte aligned rows, vector loads
-    _topk_case(P, x, 6, ld=3005)   # misaligned rows, scalar loads
+    _topk_case(P, x, 6, ld=3005)   # rows at any 2-byte address
     # rows where -inf entries must fill the list (fewer finite values than k)
     y = np.full((4, 4100), -np.inf, np.float32)
     y[0, 17] = 1.0
@@ -115,6 +115,32 @@ def test_topk_all_equal_and_strided(P):
     big = np.full((2, 200003), -np.inf, np.float32)  # sliced path
     big[0, 199999] = 2.0
     _topk_case(P, W.f32_to_bf16_bits(big), 3)
+
+
+@pytest.mark.parametrize("off,V", [(1, 1), (3, 6), (7, 9), (5, 17), (1, 4096), (2, 32767),
+                                   (3, 32776), (7, 65541), (1, 128257)])
+def test_topk_rows_at_any_address(P, off, V):
+    # the logits are a view that starts `off` elements into a buffer, with an odd
+    # row stride: every row starts at another offset from a 16-byte boundary, and
+    # the slices' first and last partial chunks hold the best and tied values
+    rng = np.random.default_rng(off + V)
+    R, k, ld = 9, min(V, 8), V + (V % 2 == 0)
+    for bf in (True, False):
+        x = rng.standard_normal((R, V), dtype=np.float32)
+        x[:, :min(V, 4)] += 3.0
+        x[1::2, -1:] = 5.0
+        x[2::3, V // 2] = 5.0
+        bits = W.f32_to_bf16_bits(x)
+        arr = (bits.astype(np.uint32) << 16).view(np.float32) if bf else x
+        buf = torch.full((off + R * ld,), 1e30, device="cuda",
+                         dtype=torch.bfloat16 if bf else torch.float32)
+        lg = buf[off:].view(R, ld)[:, :V]
+        lg.copy_(cu(arr))
+        am, idx, val = P.topk_argmax(lg, k)
+        order = np.stack([np.lexsort((np.arange(V), -r)) for r in arr])[:, :k]
+        assert np.array_equal(idx.cpu().numpy(), order)
+        assert np.array_equal(am.cpu().numpy(), order[:, 0])
+        assert np.array_equal(val.cpu().numpy(), np.take_along_axis(arr, order, 1))
 
 
 @pytest.mark.parametrize("k", [1, 4, 16])
