@@ -191,3 +191,28 @@ def test_sample_deterministic(P):
     r1 = [t.cpu() for t in P.verify_sample(*args)]
     r2 = [t.cpu() for t in P.verify_sample(*args)]
     assert all(torch.equal(a, b) for a, b in zip(r1, r2))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [1, 9, 2047, 2049, 4103])
+@pytest.mark.parametrize("kind", ["plain", "masked", "far"])
+def test_sample_odd_rows_masks_and_far_logits(P, dtype, V, kind):
+    # rows that start at any element address (odd strides; block edges), masked
+    # vocabulary entries (-inf and the type's lowest value, a whole block of
+    # them too), and logits whose exponents leave the fp32 fast range
+    rng = np.random.default_rng(V + len(kind))
+    B, T = 4, 12
+    par = np.stack([W.tree_uniform(rng, T)[0] for _ in range(B)])
+    x = (rng.standard_normal((B, T + 1, V)) * 2.0).astype(np.float32)
+    if kind == "masked" and V > 8:
+        x[:, :, rng.choice(V, V // 3, replace=False)] = -np.inf
+        x[:, :, rng.choice(V, V // 4, replace=False)] = np.float32(-3.3e38)
+        if V > 4096:
+            x[:, :, 2048:4096] = -np.inf
+    if kind == "far":
+        x = x * np.float32(40.0) + np.float32(3000.0)
+    lg = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    lf = W.bf16_bits_to_f32(lg) if dtype == "bf16" else lg
+    tok = likely_tokens(rng, lf, par, top=min(3, V))
+    for ld in (None, V + 3):
+        sample_case(P, lg, tok, par, 1.0, rng.random((B, T)), rng.random((B, T + 1)), ld=ld)
