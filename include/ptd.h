@@ -149,13 +149,14 @@ size_t ptd_tree_attention_workspace_bytes(const ptd_attn_shape* shape, int32_t T
  *   out      [B][T][Hq][D]           out_dtype (fp32 accumulation inside)
  *   shape    host struct above
  *   mask     uint64 [B][T][ceil(T/64)] from ptd_build_tree_mask, or NULL to
- *            have it built into the workspace.  Read only by the fp32 path
- *            and for T > 128: with bf16 inputs and T <= 128 the kernel derives
- *            every row's ancestor words from parent itself (mask ignored).
+ *            have the ancestors found from parent (built into the workspace
+ *            for T > 128).  Read only for T > 128 and by the fp32 path: with
+ *            bf16 inputs and T <= 128 the kernel derives every row's ancestor
+ *            words from parent itself (mask ignored).
  *   workspace, workspace_bytes: device scratch of at least
  *            ptd_tree_attention_workspace_bytes(shape, T) bytes, 256-byte aligned
  * Pointers to q/k/v/out must be 16-byte aligned.  in_dtype bf16 runs on MFMA
- * (v_mfma_f32_16x16x32_bf16); fp32 inputs run on the vector ALUs.
+ * (v_mfma_f32_16x16x32_bf16), fp32 inputs on v_mfma_f32_16x16x4_f32.
  * dev_status: PTD_ERR_BAD_TREE, PTD_ERR_KV_LEN.
  * Errors: PTD_ERR_NULL, PTD_ERR_SHAPE, PTD_ERR_DTYPE, PTD_ERR_ALIGN,
  * PTD_ERR_WORKSPACE, PTD_ERR_HIP.

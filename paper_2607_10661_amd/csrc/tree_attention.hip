@@ -24,9 +24,10 @@
 //                  chains with wave shuffles.  With the keys split over
 //                  several workgroups, each writes fp32 partials (m, l, O).
 //   k_attn_combine merges split-KV partials in a fixed split order.
-//   k_attn_valu    fp32 (or bf16) inputs on the vector ALUs, fp32 throughout.
+//   k_attn_f32     fp32 inputs: v_mfma_f32_16x16x4_f32, fp32 throughout.
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -66,7 +67,7 @@ struct AttnParams {
   const int32_t* tree_len;  // [B] or null: nodes at index >= tree_len[b] are padding
   const float* k_scale;     // [Hkv] or null (8-bit caches): key = code value * k_scale[g]
   const float* v_scale;     // [Hkv] or null: value = code value * v_scale[g]
-  const uint64_t* mask;   // [B][T][W] ancestor words (trees of more than 128 nodes, fp32 path)
+  const uint64_t* mask;   // [B][T][W] ancestor words (trees of more than 128 nodes; fp32 when given)
   void* out;
   float* part_o;    // [S][B][Hkv][M][D]
   float2* part_ml;  // [S][B][Hkv][M]: (running max * c, sum of p)
@@ -1023,8 +1024,12 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
 // consecutive rows of one (b, g): everything per (b, g) is uniform (scalar
 // loads and arithmetic) and a thread's row and columns are shifts of its id.
 // ===========================================================================
-template <int D, int U>
+template <int D, int U, bool F32>
 __global__ void __launch_bounds__(256) k_attn_combine(AttnParams p) {
+  // partial maxima are in the exp2 domain, or (fp32 path) scores as they are
+  auto expo = [](float x) __attribute__((always_inline)) {
+    return F32 ? expf(x) : __builtin_amdgcn_exp2f(x);
+  };
   constexpr int D4 = D / 4;
   constexpr int RPB = 256 / D4;  // rows per workgroup
   const int nrb = (p.M + RPB - 1) / RPB;
@@ -1064,8 +1069,8 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnParams p) {
     for (int u = 0; u < U; ++u) {
       const bool live = s0 + u < nsp;
       const float mn = fmaxf(mrun, ml[u].x);
-      const float a = __builtin_amdgcn_exp2f(mrun - mn);
-      const float w = __builtin_amdgcn_exp2f(ml[u].x - mn);
+      const float a = expo(mrun - mn);
+      const float w = expo(ml[u].x - mn);
       const f32x4 na = acc * a + ov[u] * w;
       den = live ? den * a + w * ml[u].y : den;
 #pragma unroll
@@ -1092,25 +1097,69 @@ __global__ void __launch_bounds__(256) k_attn_combine(AttnParams p) {
 }
 
 // ===========================================================================
-// vector-ALU path (fp32 inputs): one workgroup of 256 threads per (b, g, pass
-// of 32 rows); 64-key tiles; lane j of a wave scores key j of the tile for one
-// query row at a time; the running state of every row lives in LDS.
+// fp32 path: v_mfma_f32_16x16x4_f32 (fp32 products and sums).  One workgroup of
+// 8 waves per (b, g, 16 query rows, KV split); wave w takes the 16-key tiles
+// w, w + 8, .. of the split with a softmax state of its own, and the states
+// merge through LDS at the end.
+//   S^T = K Q^T per tile: lane (l16, l4) holds K[key l16][16 j + 4 l4 + e] and
+//   Q[row l16][same], one 16-byte load each per 16 columns; the MFMA of (j, e)
+//   contracts the columns 16 j + 4 l4 + e over the four lane groups.  The lane
+//   then owns scores of query l16 and keys 4 l4 + e.
+//   O^T += V^T P^T: the MFMA of step e contracts the keys 4 l4 + e, whose p the
+//   lane owns already; its A operand for the columns {64 h + 4 i + f} is element
+//   f of the 16 bytes V[4 l4 + e][64 h + 4 l16 ..].  No operand passes LDS.
+// The next tile's K and this tile's V load while the scores are formed.  Bound by
+// latency at the sizes of a reference configuration (2 heads x 16 rows x 144
+// keys: 7.9 us for the kernel; one workgroup of vector dot products per (b, g, 32
+// rows), one key per lane, took 37.6 and a mask pass before it 1.8; 4 heads x 64
+// rows x 576 keys x 128 columns, a whole step of it: 33 against 321 us).
 // ===========================================================================
-constexpr int kValuThreads = 256;
-constexpr int kValuRows = 32;
+constexpr int kF32Threads = 512;
+constexpr int kF32Waves = kF32Threads / PTD_WAVE;
+constexpr int kF32Rows = 16;
+constexpr int kF32Keys = 16;
+
+// Ancestor words (nodes 0-63, 64-127) of a node of a tree of up to 128 nodes:
+// lane x of the wave holds parent[x] and parent[x + 64] (-1 past the tree).
+// Every lane takes part; each step moves to a lower index.
+__device__ __forceinline__ void ancestor_words(int node, int par_lo, int par_hi, int32_t* dev_status,
+                                               uint64_t& w0, uint64_t& w1) {
+  int a = node;
+  w0 = w1 = 0ull;
+  for (int step = 0; step < 128; ++step) {
+    if (!__any(a >= 0)) break;
+    const uint64_t bit = 1ull << (a & 63);
+    w0 |= (a >= 0 && a < 64) ? bit : 0ull;
+    w1 |= (a >= 64) ? bit : 0ull;
+    const int plo = __shfl(par_lo, a & 63, PTD_WAVE);
+    const int phi = __shfl(par_hi, a & 63, PTD_WAVE);
+    int nx = a >= 64 ? phi : plo;
+    if (a < 0) {
+      nx = -1;
+    } else if (nx < -1 || nx >= a) {  // not topological
+      ptd::report(dev_status, PTD_ERR_BAD_TREE);
+      nx = -1;
+    }
+    a = nx;
+  }
+}
 
 template <int D>
-__global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnParams p) {
-  constexpr int KT = 64;
-  constexpr int DU = D / 64;  // output columns per lane
-  __shared__ float ks[KT][D + 1];
-  __shared__ float vs[KT][D];
-  __shared__ float qs[kValuRows][D];
-  __shared__ float acc[kValuRows][D];
-  __shared__ float sm[kValuRows], sl[kValuRows];
-
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int pass = blockIdx.x, g = blockIdx.y, b = blockIdx.z;
+__global__ void __launch_bounds__(kF32Threads, 2) k_attn_f32(AttnParams p) {
+  constexpr int KJ = D / 16;  // 16-byte loads of a K or Q fragment
+  constexpr int H = D / 64;   // 64-column halves of V and O
+  __shared__ __attribute__((aligned(16))) float so[kF32Waves][kF32Rows][D];
+  __shared__ float2 sml[kF32Waves][kF32Rows];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, l4 = lane >> 4;
+  int id;
+  logical_block(gridDim.x, p.B * p.Hkv, false, id);
+  const int split = id % p.splits;
+  int rest = id / p.splits;
+  const int r0 = (rest % p.passes) * kF32Rows;
+  rest /= p.passes;
+  const int g = rest % p.Hkv, b = rest / p.Hkv;
   const int n_kv = p.kv_len[b];
   const int tl = live_nodes(p, b);
   if (n_kv < 0 || n_kv > p.L_cap - tl) {  // (no overflow near the int range)
@@ -1118,83 +1167,143 @@ __global__ void __launch_bounds__(kValuThreads) k_attn_valu(AttnParams p) {
     return;
   }
   const int N = n_kv + tl;
-  const int r0 = pass * kValuRows;
-  const float* qg = static_cast<const float*>(p.q);
-  const float* kg = static_cast<const float*>(p.k);
-  const float* vg = static_cast<const float*>(p.v);
-  for (int x = tid; x < kValuRows * D; x += kValuThreads) {
-    const int rl = x / D, d = x % D, r = r0 + rl;
-    float v = 0.f;
-    if (r < p.M) {
-      const int i = r / p.G, hg = r % p.G;
-      v = qg[((static_cast<size_t>(b) * p.T + i) * p.Hq + g * p.G + hg) * D + d];
-    }
-    qs[rl][d] = v;
-    acc[rl][d] = 0.f;
-  }
-  if (tid < kValuRows) {
-    sm[tid] = kNegBig;
-    sl[tid] = 0.f;
-  }
+  const int csz = chunk_size(N, p.splits);
+  const int start = split * csz, end = min(N, start + csz);
+  if (p.splits > 1 && start >= end) return;  // empty split: the combine skips it
+
+  // this lane's query row (padding nodes read row 0; their output is zero)
+  const int r = min(r0 + l16, p.M - 1);
+  const int node = r / p.G < tl ? r / p.G : 0;
+  const bool live = r / p.G < tl;
+  const float* qr = static_cast<const float*>(p.q) +
+                    ((static_cast<size_t>(b) * p.T + node) * p.Hq + g * p.G + r % p.G) * D + 4 * l4;
   const size_t kvoff = (static_cast<size_t>(b) * p.Hkv + g) * p.L_cap * D;
-  for (int t0 = 0; t0 < N; t0 += KT) {
-    __syncthreads();
-    for (int x = tid; x < KT * D; x += kValuThreads) {
-      const int kk = x / D, d = x % D;
-      const int row = min(t0 + kk, N - 1);
-      ks[kk][d] = kg[kvoff + static_cast<size_t>(row) * D + d];
-      vs[kk][d] = vg[kvoff + static_cast<size_t>(row) * D + d];
+  const float* kb = static_cast<const float*>(p.k) + kvoff + 4 * l4;
+  const float* vb = static_cast<const float*>(p.v) + kvoff + 4 * l16;
+
+  const int ntiles = end > start ? (end - start + kF32Keys - 1) / kF32Keys : 0;
+  f32x4 qf[KJ], kf[KJ];
+  auto load_k = [&](int t) __attribute__((always_inline)) {
+    const float* src = kb + static_cast<size_t>(min(start + t * kF32Keys + l16, N - 1)) * D;
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) kf[j] = *reinterpret_cast<const f32x4*>(src + 16 * j);
+  };
+  if (wave < ntiles) {
+    load_k(wave);
+#pragma unroll
+    for (int j = 0; j < KJ; ++j) qf[j] = *reinterpret_cast<const f32x4*>(qr + 16 * j);
+  }
+  // ancestors of this lane's node, where the wave meets tree keys and no mask
+  // rows are given
+  uint64_t w0 = 0, w1 = 0;
+  if (!p.mask && end > n_kv) {
+    const int32_t* pb = p.parent + static_cast<size_t>(b) * p.T;
+    const int lo = lane < tl ? pb[lane] : -1, hi = lane + 64 < tl ? pb[lane + 64] : -1;
+    ancestor_words(live ? node : -1, lo, hi, p.dev_status, w0, w1);
+  }
+
+  f32x4 o[H][4];
+#pragma unroll
+  for (int h = 0; h < H; ++h)
+#pragma unroll
+    for (int f = 0; f < 4; ++f) o[h][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = kNegBig, l = 0.f;  // l: this lane's keys only
+  for (int t = wave; t < ntiles; t += kF32Waves) {
+    const int key0 = start + t * kF32Keys + 4 * l4;
+    f32x4 vf[4][H];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+        vf[e][h] = *reinterpret_cast<const f32x4*>(vb + static_cast<size_t>(min(key0 + e, N - 1)) * D + 64 * h);
+    f32x4 s0 = {0.f, 0.f, 0.f, 0.f}, s1 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int j = 0; j < KJ; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; e += 2) {
+        s0 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][e], qf[j][e], s0, 0, 0, 0);
+        s1 = __builtin_amdgcn_mfma_f32_16x16x4f32(kf[j][e + 1], qf[j][e + 1], s1, 0, 0, 0);
+      }
+    if (t + kF32Waves < ntiles) load_k(t + kF32Waves);
+    f32x4 s = (s0 + s1) * p.scale;
+    if (start + (t + 1) * kF32Keys > min(n_kv, end)) {  // uniform: tree keys, or past the split
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int key = key0 + e;
+        const int a = min(max(key - n_kv, 0), p.T - 1);
+        const uint64_t word = p.mask ? p.mask[(static_cast<size_t>(b) * p.T + node) * p.W + (a >> 6)]
+                                     : (a >= 64 ? w1 : w0);
+        const bool vis = key < end && (key < n_kv || ((word >> (a & 63)) & 1ull) != 0);
+        s[e] = vis ? s[e] : -INFINITY;
+      }
     }
-    __syncthreads();
-    const int key = t0 + lane;
-#pragma unroll 1
-    for (int rl = wave; rl < kValuRows; rl += kValuThreads / PTD_WAVE) {
-      const int r = r0 + rl;
-      if (r >= p.M) break;
-      const int i = r / p.G;
-      bool vis = key < N;
-      if (vis && key >= n_kv) {
-        const int a = key - n_kv;
-        vis = (p.mask[(static_cast<size_t>(b) * p.T + i) * p.W + (a >> 6)] >> (a & 63)) & 1ull;
-      }
-      float s = -INFINITY;
-      if (vis) {
-        float dot = 0.f;
-#pragma unroll 8
-        for (int d = 0; d < D; ++d) dot = fmaf(qs[rl][d], ks[lane][d], dot);
-        s = dot * p.scale;
-      }
-      const float m_old = sm[rl];
-      const float m_new = fmaxf(m_old, ptd::wave_max(s));
-      const float alpha = expf(m_old - m_new);
-      const float pj = expf(s - m_new);
-      const float psum = ptd::wave_sum(pj);
-      float a[DU];
+    float mx = fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]));
+    mx = fmaxf(m, max_xor32(max_xor16(mx)));
+    const float alpha = expf(m - mx);
+    m = mx;
+    f32x4 pr;
 #pragma unroll
-      for (int u = 0; u < DU; ++u) a[u] = acc[rl][lane + 64 * u] * alpha;
-#pragma unroll 4
-      for (int j = 0; j < KT; ++j) {
-        const float pb = __shfl(pj, j, PTD_WAVE);
+    for (int e = 0; e < 4; ++e) pr[e] = expf(s[e] - mx);
+    l = l * alpha + ((pr[0] + pr[1]) + (pr[2] + pr[3]));
 #pragma unroll
-        for (int u = 0; u < DU; ++u) a[u] = fmaf(pb, vs[j][lane + 64 * u], a[u]);
-      }
+    for (int h = 0; h < H; ++h)
 #pragma unroll
-      for (int u = 0; u < DU; ++u) acc[rl][lane + 64 * u] = a[u];
-      if (lane == 0) {
-        sl[rl] = sl[rl] * alpha + psum;
-        sm[rl] = m_new;
-      }
-    }
+      for (int f = 0; f < 4; ++f) o[h][f] *= alpha;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+#pragma unroll
+      for (int h = 0; h < H; ++h)
+#pragma unroll
+        for (int f = 0; f < 4; ++f)
+          o[h][f] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[e][h][f], pr[e], o[h][f], 0, 0, 0);
+  }
+
+  // merge of the waves: lane (l16, l4) holds query l16, columns
+  // 64 h + 16 l4 + 4 x + f of O in o[h][f][x]
+  l = sum_xor32(sum_xor16(l));
+  if (l4 == 0) sml[wave][l16] = make_float2(m, l);
+  if (wave < ntiles) {
+#pragma unroll
+    for (int h = 0; h < H; ++h)
+#pragma unroll
+      for (int x = 0; x < 4; ++x)
+        *reinterpret_cast<f32x4*>(&so[wave][l16][64 * h + 16 * l4 + 4 * x]) =
+            f32x4{o[h][0][x], o[h][1][x], o[h][2][x], o[h][3][x]};
   }
   __syncthreads();
-  for (int x = tid; x < kValuRows * D; x += kValuThreads) {
-    const int rl = x / D, d = x % D, r = r0 + rl;
-    if (r >= p.M) continue;
-    const int i = r / p.G, hg = r % p.G;
+  const int nw = min(ntiles, kF32Waves);
+  for (int x = tid; x < kF32Rows * D / 4; x += kF32Threads) {
+    const int row = x / (D / 4), d = (x % (D / 4)) * 4;
+    const int rr = r0 + row;
+    if (rr >= p.M) break;
+    float mm = kNegBig;
+    for (int w = 0; w < nw; ++w) mm = fmaxf(mm, sml[w][row].x);
+    float den = 0.f;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int w = 0; w < nw; ++w) {
+      const float2 ml = sml[w][row];
+      const float f = expf(ml.x - mm);
+      den = fmaf(f, ml.y, den);
+      acc += *reinterpret_cast<const f32x4*>(&so[w][row][d]) * f;
+    }
+    if (p.splits > 1) {
+      const size_t prow = ((static_cast<size_t>(split) * p.B + b) * p.Hkv + g) * p.M + rr;
+      *reinterpret_cast<f32x4*>(p.part_o + prow * D + d) = acc;
+      if (d == 0) p.part_ml[prow] = make_float2(mm, den);
+      continue;
+    }
+    const int i = rr / p.G, hg = rr % p.G;
     const size_t off = ((static_cast<size_t>(b) * p.T + i) * p.Hq + g * p.G + hg) * D + d;
-    const float v = i < tl ? acc[rl][d] / sl[rl] : 0.f;  // padding nodes: zero
-    if (p.out_bf16) static_cast<uint16_t*>(p.out)[off] = static_cast<uint16_t>(ptd::f32_to_bf16_rne(v));
-    else static_cast<float*>(p.out)[off] = v;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};  // padding nodes: zero
+    if (i < tl)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[e] = acc[e] / den;
+    if (p.out_bf16) {
+      const u32x2 w = {ptd::cvt_pk_bf16(v[0], v[1]), ptd::cvt_pk_bf16(v[2], v[3])};
+      *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(p.out) + off) = w;
+    } else {
+      *reinterpret_cast<f32x4*>(static_cast<float*>(p.out) + off) = v;
+    }
   }
 }
 
@@ -1205,7 +1314,7 @@ struct Plan {
   bool mfma;
   int QB, WR, passes, rows_per_pass, splits;
   int nt;  // threads per k_attn_mfma workgroup (512, or 256 with two workgroups per CU)
-  bool needs_mask;  // mask rows read from memory (fp32 path, trees over 128 nodes)
+  bool needs_mask;  // workspace has room for mask rows (fp32 inputs, trees over 128 nodes)
   // workspace: [partials][mask rows], each 256-byte aligned
   size_t partial_bytes, mask_bytes, total_bytes;
 };
@@ -1267,16 +1376,21 @@ bool make_plan(const ptd_attn_shape* s, int T, Plan* pl) {
     if (sp > 64) sp = 64;
     pl->splits = sp;
   } else {
+    // fp32: 16-row workgroups; the keys are split while workgroups are fewer
+    // than CUs and a split keeps at least 512 keys x 64 columns (about 4 us of
+    // matrix work; the combine of the splits costs about as much)
     pl->WR = pl->QB = 0;
-    pl->nt = kValuThreads;
-    pl->rows_per_pass = kValuRows;
-    pl->passes = static_cast<int>((M + kValuRows - 1) / kValuRows);
-    pl->splits = 1;
+    pl->nt = kF32Threads;
+    pl->rows_per_pass = kF32Rows;
+    pl->passes = static_cast<int>((M + kF32Rows - 1) / kF32Rows);
+    const long long items = static_cast<long long>(s->B) * s->Hkv * pl->passes;
+    const int max_by_len = static_cast<int>((static_cast<long long>(s->L_cap) * (s->D / 64) + 511) / 512);
+    pl->splits = static_cast<int>(std::min<long long>(std::max<long long>(kTargetBlocks / items, 1), std::min(max_by_len, 64)));
   }
   if (static_cast<long long>(s->B) * s->Hkv * pl->passes * pl->splits > 0x7FFFFFFFLL) return false;
   // the combine's grid: one workgroup per 8 (D = 128) or 16 (D = 64) rows of a (b, g)
   if (pl->splits > 1 && static_cast<long long>(s->B) * s->Hkv * ((M + 7) / 8) > 0x7FFFFFFFLL) return false;
-  pl->needs_mask = !pl->mfma || T > 128;
+  pl->needs_mask = !pl->mfma || T > 128;  // (fp32, T <= 128: room only, no mask pass)
   pl->partial_bytes = pl->splits > 1
       ? align256(static_cast<size_t>(pl->splits) * s->B * s->Hkv * M * (s->D + 2) * sizeof(float))
       : 0;
@@ -1361,8 +1475,16 @@ int attention_impl(const void* q, const void* k_cache, const void* v_cache,
   PTD_RETURN_IF(!ptd_aligned(q, 16) || !ptd_aligned(k_cache, 16) || !ptd_aligned(v_cache, 16) ||
                     !ptd_aligned(out, 16) || (mask && !ptd_aligned(mask, 8)),
                 PTD_ERR_ALIGN);
-  const bool build_mask = pl.needs_mask && !mask;
-  const size_t need = pl.partial_bytes + (build_mask ? pl.mask_bytes : 0);
+  if (!pl.mfma) PTD_RETURN_IF(shape->Hkv > 65535 || shape->B > 65535, PTD_ERR_SHAPE);
+  const size_t mask_need = pl.needs_mask && !mask ? pl.mask_bytes : 0;
+  // fp32 inputs: the split is an option, taken where its partials fit the scratch
+  if (!pl.mfma && pl.splits > 1 &&
+      pl.partial_bytes + mask_need > (noalloc ? PTD_NOALLOC_SCRATCH_BYTES : workspace ? workspace_bytes : 0)) {
+    pl.splits = 1;
+    pl.partial_bytes = 0;
+  }
+  const bool build_mask = mask_need > 0 && T > 128;
+  const size_t need = pl.partial_bytes + mask_need;
   if (noalloc && need > 0) {  // the fixed scratch array stands in for the workspace
     PTD_RETURN_IF(need > PTD_NOALLOC_SCRATCH_BYTES, PTD_ERR_SCRATCH);
     workspace = scratch_device_ptr();
@@ -1391,7 +1513,7 @@ int attention_impl(const void* q, const void* k_cache, const void* v_cache,
   prm.tree_len = tree_len;
   prm.k_scale = k_scale;
   prm.v_scale = v_scale;
-  prm.mask = pl.needs_mask ? mask : nullptr;
+  prm.mask = pl.needs_mask ? mask : nullptr;  // (fp32, T <= 128: used when given)
   prm.out = out;
   prm.part_o = pl.splits > 1 ? reinterpret_cast<float*>(ws) : nullptr;
   prm.part_ml = nullptr;
@@ -1422,25 +1544,27 @@ int attention_impl(const void* q, const void* k_cache, const void* v_cache,
     if (f8) launch_mfma<128, true>(pl, prm, st);  // (D = 128 checked by the entry point)
     else if (shape->D == 128) launch_mfma<128, false>(pl, prm, st);
     else launch_mfma<64, false>(pl, prm, st);
-    if (pl.splits > 1) {
-      const int rpb = 256 / (shape->D / 4);  // rows per combine workgroup
-      const dim3 grid(static_cast<unsigned>(static_cast<long long>(prm.B) * prm.Hkv *
-                                            ((prm.M + rpb - 1) / rpb)));
-      // U = splits loaded at once: the fewest of 2, 4, 8, 16 covering them
-      // (16 splits in one group of loads rather than two: 72.4 against 76.4
-      // us per call on 8 KV heads x 256 rows x 32832 keys)
-      const int u = pl.splits <= 2 ? 2 : pl.splits <= 4 ? 4 : pl.splits <= 8 ? 8 : 16;
-#define PTD_COMBINE(d_, u_) \
-  if (shape->D == d_ && u == u_) hipLaunchKernelGGL((k_attn_combine<d_, u_>), grid, dim3(256), 0, st, prm);
-      PTD_COMBINE(128, 2) PTD_COMBINE(128, 4) PTD_COMBINE(128, 8) PTD_COMBINE(128, 16)
-      PTD_COMBINE(64, 2) PTD_COMBINE(64, 4) PTD_COMBINE(64, 8) PTD_COMBINE(64, 16)
-#undef PTD_COMBINE
-    }
   } else {
-    const dim3 grid(pl.passes, prm.Hkv, prm.B);
-    PTD_RETURN_IF(prm.Hkv > 65535 || prm.B > 65535, PTD_ERR_SHAPE);
-    if (shape->D == 128) hipLaunchKernelGGL(k_attn_valu<128>, grid, dim3(kValuThreads), 0, st, prm);
-    else hipLaunchKernelGGL(k_attn_valu<64>, grid, dim3(kValuThreads), 0, st, prm);
+    const dim3 grid(prm.B * prm.Hkv * pl.passes * pl.splits);
+    if (shape->D == 128) hipLaunchKernelGGL(k_attn_f32<128>, grid, dim3(kF32Threads), 0, st, prm);
+    else hipLaunchKernelGGL(k_attn_f32<64>, grid, dim3(kF32Threads), 0, st, prm);
+  }
+  if (pl.splits > 1) {
+    const int rpb = 256 / (shape->D / 4);  // rows per combine workgroup
+    const dim3 grid(static_cast<unsigned>(static_cast<long long>(prm.B) * prm.Hkv *
+                                          ((prm.M + rpb - 1) / rpb)));
+    // U = splits loaded at once: the fewest of 2, 4, 8, 16 covering them
+    // (16 splits in one group of loads rather than two: 72.4 against 76.4
+    // us per call on 8 KV heads x 256 rows x 32832 keys)
+    const int u = pl.splits <= 2 ? 2 : pl.splits <= 4 ? 4 : pl.splits <= 8 ? 8 : 16;
+#define PTD_COMBINE(d_, u_)                                                                      \
+  if (shape->D == d_ && u == u_) {                                                               \
+    if (pl.mfma) hipLaunchKernelGGL((k_attn_combine<d_, u_, false>), grid, dim3(256), 0, st, prm); \
+    else hipLaunchKernelGGL((k_attn_combine<d_, u_, true>), grid, dim3(256), 0, st, prm);        \
+  }
+    PTD_COMBINE(128, 2) PTD_COMBINE(128, 4) PTD_COMBINE(128, 8) PTD_COMBINE(128, 16)
+    PTD_COMBINE(64, 2) PTD_COMBINE(64, 4) PTD_COMBINE(64, 8) PTD_COMBINE(64, 16)
+#undef PTD_COMBINE
   }
   return ptd_launch_status();
 }

@@ -505,6 +505,38 @@ def test_attention_fp32_full(P, spec):
     assert np.abs(got - ref).max() <= TOL["f32"]
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("Hq,Hkv,T,kv", [(1, 1, 1, [0, 15]), (2, 2, 16, [0, 16]),
+                                         (2, 1, 17, [1, 127]), (6, 2, 65, [300, 40]),
+                                         (2, 2, 128, [129, 2000]), (2, 1, 130, [5, 1500]),
+                                         (4, 4, 8, [5000, 0])])
+def test_attention_fp32_tiles_splits_and_padding(P, D, Hq, Hkv, T, kv):
+    # 16-row and 16-key tile edges, KV splits (with and without room for their
+    # partials), masks given or derived, padded trees with garbage in the padding
+    w = W.make_workload(_spec(dtype="f32", D=D, Hq=Hq, Hkv=Hkv, T=T, B=2, kv_len=kv), seed=T + D,
+                        logits=False)
+    q, kc, vc, kvl, par = cu(w.q), cu(w.k_cache), cu(w.v_cache), cu(w.kv_len), cu(w.parent)
+    ref = O.tree_attention(w.q, w.k_cache, w.v_cache, w.kv_len, w.parent, w.scale)
+    mask = P.tree_mask(par)[0]
+    small = torch.empty(((2 * T * ((T + 63) // 64) * 8 + 255) // 256) * 256, dtype=torch.uint8,
+                        device="cuda")  # the masks' room only: one split
+    for m, ws in ((None, None), (mask, None), (None, small)):
+        st = status_buf()
+        got = P.tree_attention(q, kc, vc, kvl, par, mask=m, workspace=ws, dev_status=st)
+        assert st.item() == 0
+        assert np.abs(got.cpu().numpy() - ref).max() <= TOL["f32"]
+    live = np.array([max(0, T - 3), (T + 1) // 2], np.int32)
+    par2, q2 = par.clone(), q.clone()
+    for b in range(2):
+        par2[b, live[b]:] = 7777
+        q2[b, live[b]:] = float("nan")
+    r2 = O.tree_attention(w.q, w.k_cache, w.v_cache, w.kv_len, w.parent, w.scale, tree_len=live)
+    st = status_buf()
+    got = P.tree_attention(q2, kc, vc, kvl, par2, dev_status=st, tree_len=cu(live))
+    assert st.item() == 0
+    assert np.abs(got.cpu().numpy() - r2).max() <= TOL["f32"]
+
+
 def test_attention_tiny_config(P):
     w = W.make_workload("tiny", logits=False)
     ref = O.tree_attention(w.q, w.k_cache, w.v_cache, w.kv_len, w.parent, w.scale)
