@@ -208,7 +208,7 @@ __device__ __forceinline__ u32x4 gload16(const void* p) {
 // Orders every later use of v after the preceding (volatile) wait.
 __device__ __forceinline__ void reg_fence(u32x4& v) { asm volatile("" : "+v"(v)); }
 
-template <int D, int QB, int WR, bool F8, int NT = kThreads>
+template <int D, int QB, int WR, bool F8, bool PAGED, int NT = kThreads>
 __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   // F8: keys and values are OCP E4M3 codes (scaled per KV head), widened to
   // bf16 exactly after the LDS reads; everything else is the bf16 kernel
@@ -286,16 +286,15 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
     return;
   }
 
-  const bool paged = p.page_table != nullptr;  // uniform
   const KV* kbase = static_cast<const KV*>(p.k) +
-                    (paged ? 0 : (static_cast<size_t>(b) * p.Hkv + g) * p.L_cap * D);
+                    (PAGED ? 0 : (static_cast<size_t>(b) * p.Hkv + g) * p.L_cap * D);
   const KV* vbase = static_cast<const KV*>(p.v) +
-                    (paged ? 0 : (static_cast<size_t>(b) * p.Hkv + g) * p.L_cap * D);
+                    (PAGED ? 0 : (static_cast<size_t>(b) * p.Hkv + g) * p.L_cap * D);
   // paged: the split's first 256 page ids, one per lane and register, loaded
   // untracked ahead of the query rows
-  const int first_page = paged ? (start >> p.page_shift) : 0;
+  const int first_page = PAGED ? (start >> p.page_shift) : 0;
   u32x4 pg = {0u, 0u, 0u, 0u};
-  if (paged) {
+  if constexpr (PAGED) {
     const int npg = ((end - 1) >> p.page_shift) - first_page + 1;
     const int32_t* pt = p.page_table + static_cast<size_t>(b) * p.max_pages + first_page;
 #pragma unroll
@@ -318,7 +317,7 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
 #pragma unroll
     for (int db = 0; db < DB; ++db) qraw[qb][db] = gload16(src + 32 * db);
   }
-  if (paged) {  // the page ids (issued before the query rows) are needed by the first copy
+  if constexpr (PAGED) {  // the page ids (issued before the query rows) are needed by the first copy
     wait_vmcnt_le(QB * DB);
     reg_fence(pg);
     const int npg = ((end - 1) >> p.page_shift) - first_page + 1;
@@ -350,20 +349,29 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
     cp_voff[u] = static_cast<uint32_t>((cp_row[u] * D + cp_off[u]) * ES);
     cp_lds[u] = static_cast<uint32_t>((u * NT + wave * PTD_WAVE) * 16);
   }
+  // physical page of the split's ti-th page, ti < 256 (staged in pg)
+  auto staged_page = [&](int ti) __attribute__((always_inline)) -> uint32_t {
+    const uint32_t v0 = __builtin_amdgcn_readlane(pg[0], ti & 63);
+    const uint32_t v1 = __builtin_amdgcn_readlane(pg[1], ti & 63);
+    const uint32_t v2 = __builtin_amdgcn_readlane(pg[2], ti & 63);
+    const uint32_t v3 = __builtin_amdgcn_readlane(pg[3], ti & 63);
+    const int k = ti >> 6;
+    return k == 0 ? v0 : k == 1 ? v1 : k == 2 ? v2 : v3;
+  };
+  // element offset of key row `row0` in its page
+  auto page_offset = [&](uint32_t phys, int row0) __attribute__((always_inline)) -> size_t {
+    return (((static_cast<size_t>(phys) * p.Hkv + g) << p.page_shift) +
+            (row0 & ((1 << p.page_shift) - 1))) * D;
+  };
   // element offset of key row `row0` (a multiple of 32): contiguous, or in
   // its page (a page holds a multiple of 32 rows, so the sub-tile's 32 rows
   // are consecutive there)
   auto tile_offset = [&](int row0) __attribute__((always_inline)) -> size_t {
-    if (!paged) return static_cast<size_t>(row0) * D;
+    if constexpr (!PAGED) return static_cast<size_t>(row0) * D;
     const int ti = (row0 >> p.page_shift) - first_page;  // uniform
     uint32_t phys;
     if (ti < 4 * PTD_WAVE) {
-      const uint32_t v0 = __builtin_amdgcn_readlane(pg[0], ti & 63);
-      const uint32_t v1 = __builtin_amdgcn_readlane(pg[1], ti & 63);
-      const uint32_t v2 = __builtin_amdgcn_readlane(pg[2], ti & 63);
-      const uint32_t v3 = __builtin_amdgcn_readlane(pg[3], ti & 63);
-      const int k = ti >> 6;
-      phys = k == 0 ? v0 : k == 1 ? v1 : k == 2 ? v2 : v3;
+      phys = staged_page(ti);
     } else {  // beyond the staged ids: a scalar load (checked the same way)
       phys = static_cast<uint32_t>(
           p.page_table[static_cast<size_t>(b) * p.max_pages + (row0 >> p.page_shift)]);
@@ -372,9 +380,7 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
         phys = 0u;
       }
     }
-    const size_t prow = ((static_cast<size_t>(phys) * p.Hkv + g) << p.page_shift) +
-                        (row0 & ((1 << p.page_shift) - 1));
-    return prow * D;
+    return page_offset(phys, row0);
   };
   // copy sub-tile t (keys start + 32t ..) into ring slot `slot`
   auto issue = [&](int t, int slot) __attribute__((always_inline)) {
@@ -809,8 +815,7 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
       }
       cs = ns;
   };
-  // Steady rounds: every refill of the round is a whole sub-tile of a
-  // contiguous cache below t_mask0, so this round's and the next round's
+  // Steady rounds: every refill of the round is a whole sub-tile below t_mask0, so this round's and the next round's
   // sub-tiles need no masking either; the wait count is the constant, the
   // tile address scalar arithmetic, and the general round's tests drop out
   // (with and without the software pipeline; without it, 34.9 against 36.7 us
@@ -824,15 +829,26 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   // so the main path is one block the scheduling groups below can interleave
   // (the precise test still reads the row sums before this sub-tile, and
   // every accumulator receives hi before lo as in the general round).
-  const int steady_hi =
-      (!paged && t_mask0 >= R::NS + WK) ? (t_mask0 - R::NS - WK) / WK + 1 : 0;
+  // Paged caches: a refill's page id is one of the 256 staged in registers
+  // (scalar lane reads); beyond those the general round reads the table
+  // (16 sequences of 512-8192 keys on 64-row pages: 114.3 against 121.2 us per
+  // call with general rounds only; 6 of 1024-16384 on E4M3 pages 69.6 against 71.6).
+  int t_steady = t_mask0;
+  if constexpr (PAGED) {
+    const long long staged = (static_cast<long long>(first_page + 4 * PTD_WAVE) << p.page_shift) - start;
+    t_steady = static_cast<int>(min(static_cast<long long>(t_mask0), staged / R::SUB));
+  }
+  const int steady_hi = t_steady >= R::NS + WK ? (t_steady - R::NS - WK) / WK + 1 : 0;
   auto round_steady = [&](int rd) __attribute__((always_inline)) {
     wait_vmcnt<(R::NS - (2 + (PIPE ? 1 : 0)) * WK) * R::DPS>();
     lds_barrier();
 #pragma unroll
     for (int w = 0; w < WK; ++w) {
       const int tt = R::NS + (rd - 1) * WK + w;
-      const size_t tile = static_cast<size_t>(start + tt * R::SUB) * D;
+      const int row0 = start + tt * R::SUB;
+      size_t tile;
+      if constexpr (PAGED) tile = page_offset(staged_page((row0 >> p.page_shift) - first_page), row0);
+      else tile = static_cast<size_t>(row0) * D;
       const uint32_t slot_lds = ring + rs * R::SLOT;
       if constexpr (R::DPS == 1) {
         dma16_s((cp_v[0] ? vbase : kbase) + tile, cp_voff[0], slot_lds + cp_lds[0]);
@@ -1399,16 +1415,16 @@ bool make_plan(const ptd_attn_shape* s, int T, Plan* pl) {
   return true;
 }
 
-template <int D, bool F8>
+template <int D, bool F8, bool PAGED>
 void launch_mfma(const Plan& pl, const AttnParams& prm, hipStream_t st) {
   const dim3 grid(prm.B * prm.Hkv * pl.passes * pl.splits);
   if (pl.nt == 256) {
-    hipLaunchKernelGGL((k_attn_mfma<D, 2, 4, F8, 256>), grid, dim3(256), 0, st, prm);
+    hipLaunchKernelGGL((k_attn_mfma<D, 2, 4, F8, PAGED, 256>), grid, dim3(256), 0, st, prm);
     return;
   }
   const dim3 block(kThreads);
 #define PTD_MFMA_CASE(qb_, wr_) \
-  if (pl.QB == qb_ && pl.WR == wr_) { hipLaunchKernelGGL((k_attn_mfma<D, qb_, wr_, F8>), grid, block, 0, st, prm); return; }
+  if (pl.QB == qb_ && pl.WR == wr_) { hipLaunchKernelGGL((k_attn_mfma<D, qb_, wr_, F8, PAGED>), grid, block, 0, st, prm); return; }
   PTD_MFMA_CASE(1, 2) PTD_MFMA_CASE(2, 2) PTD_MFMA_CASE(2, 4)
 #undef PTD_MFMA_CASE
 }
@@ -1541,9 +1557,14 @@ int attention_impl(const void* q, const void* k_cache, const void* v_cache,
     prm.part_ml = reinterpret_cast<float2*>(prm.part_o + rows * shape->D);
   }
   if (pl.mfma) {
-    if (f8) launch_mfma<128, true>(pl, prm, st);  // (D = 128 checked by the entry point)
-    else if (shape->D == 128) launch_mfma<128, false>(pl, prm, st);
-    else launch_mfma<64, false>(pl, prm, st);
+    const auto launch = [&](auto paged) {
+      constexpr bool kPaged = decltype(paged)::value;
+      if (f8) launch_mfma<128, true, kPaged>(pl, prm, st);  // (D = 128 checked by the entry point)
+      else if (shape->D == 128) launch_mfma<128, false, kPaged>(pl, prm, st);
+      else launch_mfma<64, false, kPaged>(pl, prm, st);
+    };
+    if (page_table) launch(std::true_type{});
+    else launch(std::false_type{});
   } else {
     const dim3 grid(prm.B * prm.Hkv * pl.passes * pl.splits);
     if (shape->D == 128) hipLaunchKernelGGL(k_attn_f32<128>, grid, dim3(kF32Threads), 0, st, prm);

@@ -139,6 +139,18 @@ def test_paged_split_over_256_pages(P):
          rows=[(0, 5, 3), (1, 127, 0), (0, 64, 1), (1, 0, 2)])
 
 
+@pytest.mark.parametrize("kv", [8128, 8192, 8320, 8351])
+def test_paged_steady_rounds_end_at_staged_pages(P, kv):
+    # a pipelined plan in one split (two 128-row passes per KV head): the rounds
+    # whose page ids are staged end at the 256th page of 32 rows, or at the tree
+    rng = np.random.default_rng(kv)
+    B, Hkv, T, D, ps = 1, 128, 128, 64, 32
+    L = 8480
+    parent = W.tree_uniform(rng, T)[0][None]
+    case(P, rng, B, T, 2 * Hkv, Hkv, D, L, ps, np.array([kv], np.int32), parent,
+         rows=[(0, 5, 3), (0, 255, 127), (0, 128, 64)])
+
+
 def test_paged_bad_page_id_reports(P):
     rng = np.random.default_rng(9)
     B, T, Hkv, D, ps, L = 1, 8, 2, 64, 32, 256
