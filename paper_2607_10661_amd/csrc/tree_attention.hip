@@ -516,85 +516,106 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   };
 
   // ---- scores of keys past the chunk end, or of tree keys that are not
-  //      ancestors, become -inf.  For trees of <= 128 nodes the ancestor words
-  //      of the rows' nodes are derived here, at each sub-tile with tree keys
-  //      (only the last few of a sequence): every lane follows the parent
-  //      chains of its rows' nodes (parent[a] read from lane a % 64 by
-  //      shuffles, all lanes active); each step moves to a lower index, so
-  //      128 steps end every walk.  Larger trees read the mask pass's rows.
+  //      ancestors, become -inf.  The ancestor words of the rows' nodes are
+  //      held from a sub-tile to the next ones (128 nodes: word mbase and the
+  //      one after it).  For trees of <= 128 nodes they are derived here at the
+  //      first sub-tile with tree keys (only the last few of a sequence):
+  //      every lane follows the parent chains of its rows' nodes (parent[a]
+  //      read from lane a % 64 by shuffles, all lanes active); each step moves
+  //      to a lower index, so 128 steps end every walk.  Larger trees read the
+  //      mask pass's rows, two words at a time: the compiler's wait for such a
+  //      load also waits for the ring copies in flight (256 nodes x 2 sequences
+  //      of 1000-4096 keys: 60.2 us per call against 68.0 with a load per key).
   // first sub-tile reaching past the committed keys or the chunk end
   const int t_mask0 = max(0, (min(n_kv, end) - start) / R::SUB);
+  uint64_t mw0[QB], mw1[QB];
+  int mbase = -1;  // no words held
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb) mw0[qb] = mw1[qb] = 0ull;
+  auto node_of = [&](int qb) __attribute__((always_inline)) {
+    return min(rowbase + qb * 16 + l16, p.M - 1) / p.G;
+  };
+  auto walk_words = [&]() __attribute__((always_inline)) {
+    int a[QB];  // padding nodes see no tree keys (and their parents are not read)
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      const int node = node_of(qb);
+      a[qb] = node < tl ? node : -1;
+      mw0[qb] = mw1[qb] = 0ull;
+    }
+    for (int step = 0; step < 128; ++step) {
+      bool live = false;
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) live |= a[qb] >= 0;
+      if (!__any(live)) break;
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        const int xa = a[qb];
+        const uint64_t bit = 1ull << (xa & 63);  // branchless: no indexed word pair
+        mw0[qb] |= (xa >= 0 && xa < 64) ? bit : 0ull;
+        mw1[qb] |= (xa >= 64) ? bit : 0ull;
+        const int plo = __shfl(par_lo, xa & 63, PTD_WAVE);
+        const int phi = __shfl(par_hi, xa & 63, PTD_WAVE);
+        int nx = xa >= 64 ? phi : plo;
+        if (xa < 0) {
+          nx = -1;
+        } else if (nx < -1 || nx >= xa) {  // not topological
+          ptd::report(p.dev_status, PTD_ERR_BAD_TREE);
+          nx = -1;
+        }
+        a[qb] = nx;
+      }
+    }
+  };
   auto mask_tile = [&](Tile& x, int t) __attribute__((always_inline)) {
     if (t < t_mask0) return;
     const int abs0 = start + t * R::SUB;
-    int node[QB];
-    uint64_t mw0[QB], mw1[QB];
-#pragma unroll
-    for (int qb = 0; qb < QB; ++qb) {
-      node[qb] = min(rowbase + qb * 16 + l16, p.M - 1) / p.G;
-      mw0[qb] = 0ull;
-      mw1[qb] = 0ull;
-    }
-    if (small_tree && abs0 + R::SUB > n_kv) {
-      int a[QB];  // padding nodes see no tree keys (and their parents are not read)
-#pragma unroll
-      for (int qb = 0; qb < QB; ++qb) a[qb] = node[qb] < tl ? node[qb] : -1;
-      for (int step = 0; step < 128; ++step) {
-        bool live = false;
-#pragma unroll
-        for (int qb = 0; qb < QB; ++qb) live |= a[qb] >= 0;
-        if (!__any(live)) break;
+    const int off = abs0 - n_kv;  // node of the sub-tile's first key (uniform, > -32 with tree keys)
+    const int rem = end - abs0;   // keys before the chunk end
+    const uint32_t in_chunk = rem >= 32 ? ~0u : (1u << rem) - 1u;
+    uint32_t vis[QB];  // bit k: key abs0 + k is visible to the lane's row
+    if (off > -R::SUB) {
+      const int w = max(off, 0) >> 6;
+      if (small_tree) {
+        if (mbase < 0) {
+          walk_words();
+          mbase = 0;
+        }
+      } else if (mbase < 0 || max(off, 0) + R::SUB > (mbase + 2) * 64) {
+        mbase = w;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
-          const int xa = a[qb];
-          const uint64_t bit = 1ull << (xa & 63);  // branchless: no indexed word pair
-          mw0[qb] |= (xa >= 0 && xa < 64) ? bit : 0ull;
-          mw1[qb] |= (xa >= 64) ? bit : 0ull;
-          const int plo = __shfl(par_lo, xa & 63, PTD_WAVE);
-          const int phi = __shfl(par_hi, xa & 63, PTD_WAVE);
-          int nx = xa >= 64 ? phi : plo;
-          if (xa < 0) {
-            nx = -1;
-          } else if (nx < -1 || nx >= xa) {  // not topological
-            ptd::report(p.dev_status, PTD_ERR_BAD_TREE);
-            nx = -1;
-          }
-          a[qb] = nx;
+          const uint64_t* row = p.mask + (static_cast<size_t>(b) * p.T + node_of(qb)) * p.W;
+          mw0[qb] = w < p.W ? row[w] : 0ull;
+          mw1[qb] = w + 1 < p.W ? row[w + 1] : 0ull;
         }
+        // waited for here: a load pending at the steady loop would make the
+        // compiler wait for every ring copy inside it
+#pragma unroll
+        for (int qb = 0; qb < QB; ++qb) asm volatile("" : "+v"(mw0[qb]), "+v"(mw1[qb]));
       }
+      const int s = off - 64 * mbase;  // < 128
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) {
+        if (s < 0) vis[qb] = (static_cast<uint32_t>(mw0[qb]) << -s) | ((1u << -s) - 1u);
+        else if (s == 0) vis[qb] = static_cast<uint32_t>(mw0[qb]);
+        else if (s < 64) vis[qb] = static_cast<uint32_t>((mw0[qb] >> s) | (mw1[qb] << (64 - s)));
+        else vis[qb] = static_cast<uint32_t>(mw1[qb] >> (s - 64));
+      }
+    } else {  // committed keys only
+#pragma unroll
+      for (int qb = 0; qb < QB; ++qb) vis[qb] = ~0u;
     }
     // visibility as selects only: per-element branches writing the tile
     // through this lambda's reference were miscompiled
-    if (small_tree) {
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) {
+      const uint32_t v = (vis[qb] & in_chunk) >> (4 * l4);
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int key = abs0 + kb * 16 + l4 * 4 + e;
-          const int a = key - n_kv;
-#pragma unroll
-          for (int qb = 0; qb < QB; ++qb) {
-            const uint64_t word = a >= 64 ? mw1[qb] : mw0[qb];
-            const bool anc = ((word >> (a & 63)) & 1ull) != 0;
-            const bool vis = key < end && (key < n_kv || anc);
-            x.s[kb][qb][e] = vis ? x.s[kb][qb][e] : -INFINITY;
-          }
-        }
-    } else {
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int key = abs0 + kb * 16 + l4 * 4 + e;
-          const int a = min(max(key - n_kv, 0), p.T - 1);  // in-range row word for any key
-#pragma unroll
-          for (int qb = 0; qb < QB; ++qb) {
-            const uint64_t word = p.mask[(static_cast<size_t>(b) * p.T + node[qb]) * p.W + (a >> 6)];
-            const bool anc = ((word >> (a & 63)) & 1ull) != 0;
-            const bool vis = key < end && (key < n_kv || anc);
-            x.s[kb][qb][e] = vis ? x.s[kb][qb][e] : -INFINITY;
-          }
-        }
+        for (int e = 0; e < 4; ++e)
+          x.s[kb][qb][e] = (v & (1u << (16 * kb + e))) != 0 ? x.s[kb][qb][e] : -INFINITY;
     }
   };
 
@@ -949,6 +970,9 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
     round(0);
     for (int rd = 1; rd <= steady_hi; ++rd) round_steady(rd);
     rd0 = steady_hi + 1;
+    mbase = -1;  // no masked sub-tile yet: no words live over the steady rounds
+#pragma unroll
+    for (int qb = 0; qb < QB; ++qb) mw0[qb] = mw1[qb] = 0ull;
   }
   for (int rd = rd0; rd < nrounds; ++rd) round(rd);
   wait_vmcnt<0>();

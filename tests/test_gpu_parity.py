@@ -639,6 +639,29 @@ def test_attention_workspace_reuse(P):
             assert err <= TOL["bf16"], (n, rep, err)
 
 
+@pytest.mark.parametrize("T,Hq,Hkv,D", [(64, 2, 2, 128), (97, 8, 2, 64), (128, 4, 4, 64),
+                                        (129, 2, 1, 128), (200, 4, 1, 64), (321, 2, 2, 64),
+                                        (704, 1, 1, 64)])
+def test_attention_tree_keys_at_any_offset(P, T, Hq, Hkv, D):
+    # the 32-key sub-tiles meet the ancestor words at every kind of offset: tree
+    # keys from the first key on, at, just past and just before a word's and a
+    # sub-tile's edge; deep trees, so that every word has bits
+    rng = np.random.default_rng(T)
+    kv_len = np.array([0, 31, 33, 64, 95, 161], np.int32)
+    B, L = len(kv_len), int(kv_len.max()) + T
+    parent = np.stack([W.tree_chain(T)[0]] + [W.tree_uniform(rng, T)[0] for _ in range(B - 1)])
+    q, k, v = (W.f32_to_bf16_bits(rng.standard_normal(s).astype(np.float32))
+               for s in ((B, T, Hq, D), (B, Hkv, L, D), (B, Hkv, L, D)))
+    ref = O.tree_attention(q, k, v, kv_len, parent, 1.0 / np.sqrt(D))
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for sel in (slice(0, B), slice(1, 2), slice(4, 5)):  # a batch, single sequences
+        out = P.tree_attention(cu(q[sel]), cu(k[sel]), cu(v[sel]), cu(kv_len[sel]), cu(parent[sel]),
+                               out_dtype=torch.float32, dev_status=st)
+        torch.cuda.synchronize()
+        assert st.item() == 0
+        assert np.abs(out.cpu().numpy() - ref[sel]).max() <= TOL["bf16"]
+
+
 @pytest.mark.parametrize("T", [20, 130])
 def test_attention_bad_tree_reports(P, T):
     w = W.make_workload(_spec(T=T, kv_len=50), seed=5, logits=False)
