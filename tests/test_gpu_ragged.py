@@ -241,3 +241,31 @@ def test_ragged_paged_tree_over_128_nodes(P):
     ref = O.attention_rows(q, kc, vc, kvl, par, 1.0 / np.sqrt(D), rows, tree_len=tl)
     for n, (b, h, i) in enumerate(rows):
         assert np.abs(got[b, i, h] - ref[n]).max() <= TOL_BF16, (b, h, i)
+
+
+@pytest.mark.parametrize("extra", [0, 3000])  # one split, or several
+@pytest.mark.parametrize("T,Hq,Hkv", [(64, 8, 2), (64, 4, 4), (48, 2, 1), (160, 2, 1)])
+def test_ragged_live_rows_end_at_block_and_pass_edges(P, T, Hq, Hkv, extra):
+    # live rows that end at, before and after a wave's rows, a row pass and the
+    # tree; whole passes and waves of padding rows
+    rng = np.random.default_rng(T + Hq + extra)
+    tl = [T, 32, 33, 31, 1, 0, 8, T - 1]
+    kvl = [40, 0, 64, 5, 31, 90, 33, 200]
+    q, kc, vc, kvl, tl, par = make_case(rng, len(tl), T, Hq, Hkv, 128, kvl, tl, extra_rows=extra)
+    check(P, q, kc, vc, kvl, tl, par)
+    for b in (1, 3):  # single sequences
+        check(P, q[b:b + 1], kc[b:b + 1], vc[b:b + 1], kvl[b:b + 1], tl[b:b + 1], par[b:b + 1])
+
+
+def test_ragged_paged_no_live_node_still_checks_pages(P):
+    ps, L = 32, 128
+    kp = torch.zeros((5, 2, ps, 128), dtype=torch.bfloat16, device="cuda")
+    q = torch.zeros((1, 8, 4, 128), dtype=torch.bfloat16, device="cuda")
+    par = W.tree_chain(8)[0][None]
+    for bad, want in ((4, 0), (5, 10)):
+        table = np.array([[0, 1, bad, 99]], np.int32)  # the last page is past the keys
+        st = torch.zeros(1, dtype=torch.int32, device="cuda")
+        out = P.tree_attention_paged(q, kp, kp, cu(table), cu(np.array([70], np.int32)), cu(par),
+                                     dev_status=st, tree_len=cu(np.array([0], np.int32)))
+        torch.cuda.synchronize()
+        assert st.item() == want and not out.any()
