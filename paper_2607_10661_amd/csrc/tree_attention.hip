@@ -206,7 +206,8 @@ __device__ __forceinline__ u32x4 gload16(const void* p) {
   return v;
 }
 // Orders every later use of v after the preceding (volatile) wait.
-__device__ __forceinline__ void reg_fence(u32x4& v) { asm volatile("" : "+v"(v)); }
+template <class V>
+__device__ __forceinline__ void reg_fence(V& v) { asm volatile("" : "+v"(v)); }
 
 template <int D, int QB, int WR, bool F8, bool PAGED, int NT = kThreads>
 __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
@@ -305,15 +306,16 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   const KV* vbase = static_cast<const KV*>(p.v) +
                     (PAGED ? 0 : (static_cast<size_t>(b) * p.Hkv + g) * p.L_cap * D);
   // paged: the split's first 256 page ids, one per lane and register, loaded
-  // untracked ahead of the query rows
+  // ahead of the query rows.  (Ordinary loads: the first copy's address needs
+  // them, so the compiler's wait, which covers the query rows too, costs nothing.)
   const int first_page = PAGED ? (start >> p.page_shift) : 0;
-  u32x4 pg = {0u, 0u, 0u, 0u};
+  uint32_t pg[4] = {0u, 0u, 0u, 0u};
   if constexpr (PAGED) {
     const int npg = ((end - 1) >> p.page_shift) - first_page + 1;
     const int32_t* pt = p.page_table + static_cast<size_t>(b) * p.max_pages + first_page;
 #pragma unroll
     for (int r = 0; r < 4; ++r)
-      if (r * PTD_WAVE + lane < npg) pg[r] = ptd::gload4(pt + r * PTD_WAVE + lane);
+      if (r * PTD_WAVE + lane < npg) pg[r] = static_cast<uint32_t>(pt[r * PTD_WAVE + lane]);
   }
   const int rowbase = pr0 + wr * 16 * QB;
   const bool wave_live = rowbase < m_live;  // padding waves only copy and sync
@@ -330,16 +332,14 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
 #pragma unroll
     for (int db = 0; db < DB; ++db) qraw[qb][db] = gload16(src + 32 * db);
   }
-  if constexpr (PAGED) {  // the page ids (issued before the query rows) are needed by the first copy
-    wait_vmcnt_le(QB * DB);
-    reg_fence(pg);
-    const int npg = ((end - 1) >> p.page_shift) - first_page + 1;
+  if constexpr (PAGED) {  // an id out of range is reported and page 0 read instead
     bool bad = false;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const bool used = r * PTD_WAVE + lane < npg;
-      bad |= used && pg[r] >= static_cast<uint32_t>(p.num_pages);
-      if (!used || pg[r] >= static_cast<uint32_t>(p.num_pages)) pg[r] = 0u;  // read page 0 instead
+      if (pg[r] >= static_cast<uint32_t>(p.num_pages)) {
+        bad = true;
+        pg[r] = 0u;
+      }
     }
     if (__any(bad) && tid == 0) ptd::report(p.dev_status, PTD_ERR_PAGE);
   }
@@ -427,13 +427,12 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   //      <= 128 nodes: two per lane), loaded untracked like the query rows
   //      and, like them, before any copy
   const bool small_tree = p.W <= 2;
-  u32x4 par_raw = {0xFFFFFFFFu, 0xFFFFFFFFu, 0u, 0u};  // (parent[lane], parent[lane + 64])
-  if (small_tree) {
-    const int32_t* pb = p.parent + static_cast<size_t>(b) * p.T;
-    // 4-byte untracked loads; lanes past T keep -1
-    if (lane < p.T) par_raw[0] = ptd::gload4(pb + lane);
-    if (lane + 64 < p.T) par_raw[1] = ptd::gload4(pb + lane + 64);
-  }
+  // No branch and no default value around such a load: the compiler takes its
+  // register as written at once, so a merge with another value may copy it
+  // before the data is there.  Lanes past the tree read its last entry.
+  const int32_t* pb = p.parent + static_cast<size_t>(b) * p.T;
+  uint32_t par_raw0 = ptd::gload4(pb + min(lane, p.T - 1));
+  uint32_t par_raw1 = ptd::gload4(pb + min(lane + 64, p.T - 1));
   int par_lo = -1, par_hi = -1;
   bf16x8 qf[QB][DB];  // set from qraw once the first wait has covered the loads
 
@@ -780,9 +779,10 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
       reg_fence(qraw[qb][db]);
       qf[qb][db] = __builtin_bit_cast(bf16x8, qraw[qb][db]);
     }
-  reg_fence(par_raw);
-  par_lo = static_cast<int>(par_raw[0]);
-  par_hi = static_cast<int>(par_raw[1]);
+  reg_fence(par_raw0);
+  reg_fence(par_raw1);
+  par_lo = lane < p.T ? static_cast<int>(par_raw0) : -1;
+  par_hi = lane + 64 < p.T ? static_cast<int>(par_raw1) : -1;
 
   // rounds whose wait count is the steady-state constant: every refill so far
   // issued in full (R::NS + (rd - 1) * WK <= ntiles)
