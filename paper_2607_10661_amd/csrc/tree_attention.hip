@@ -80,6 +80,7 @@ struct AttnParams {
   int page_shift, max_pages, num_pages;
   float scale;  // softmax scale
   float c;      // scale * log2(e)
+  float precise;  // kPreciseFrac, or a smaller share
   int out_bf16;
 };
 
@@ -750,7 +751,7 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
     unsigned pmask = 0;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb)
-      pmask |= __any(!(pm[qb] <= kPreciseFrac * ls[qb][0])) ? (1u << qb) : 0u;
+      pmask |= __any(!(pm[qb] <= p.precise * ls[qb][0])) ? (1u << qb) : 0u;
 #pragma unroll
     for (int qb = 0; qb < QB; ++qb) {
       const bool precise = pmask & (1u << qb);
@@ -923,7 +924,7 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
         unsigned pmask = 0;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb)
-          pmask |= __any(!(pm[qb] <= kPreciseFrac * ls[qb][0])) ? (1u << qb) : 0u;
+          pmask |= __any(!(pm[qb] <= p.precise * ls[qb][0])) ? (1u << qb) : 0u;
         PFrag pf;
 #pragma unroll
         for (int qb = 0; qb < QB; ++qb) {
@@ -1371,7 +1372,10 @@ __global__ void __launch_bounds__(kF32Threads, 2) k_attn_f32(AttnParams p) {
 // ===========================================================================
 struct Plan {
   bool mfma;
-  int QB, WR, passes, rows_per_pass, splits;
+  int QB, WR, passes, rows_per_pass;
+  int splits;  // KV splits, the largest a call may take: sizes the partials
+  int splits_full, splits_live;  // of a call without and with tree_len
+  float precise_full, precise_live;
   int nt;  // threads per k_attn_mfma workgroup (512, or 256 with two workgroups per CU)
   bool needs_mask;  // workspace has room for mask rows (fp32 inputs, trees over 128 nodes)
   // workspace: [partials][mask rows], each 256-byte aligned
@@ -1423,17 +1427,44 @@ bool make_plan(const ptd_attn_shape* s, int T, Plan* pl) {
     pl->rows_per_pass = 16 * pl->QB * pl->WR;
     pl->passes = static_cast<int>((M + pl->rows_per_pass - 1) / pl->rows_per_pass);
     const long long items = static_cast<long long>(s->B) * s->Hkv * pl->passes;
+    const auto splits_for = [&](int target) {
+      int sp = static_cast<int>(target / items);
+      const int max_by_len = (s->L_cap + 255) / 256;  // at least ~256 keys per split
+      if (sp > max_by_len) sp = max_by_len;
+      if (sp < 1) sp = 1;
+      return sp > 64 ? 64 : sp;
+    };
     // Several sequences may differ in length (kv_len is not known here):
     // twice the workgroups, so the dispatcher can even out long and short
     // ones (measured on 16 sequences of 512-8192 keys: 151-158 against
     // 167-171 us; a single sequence was slower with it).
     const int target = pl->nt == 256 ? 3 * kTargetBlocks : s->B > 1 ? 2 * kTargetBlocks : kTargetBlocks;
-    int sp = static_cast<int>(target / items);
-    const int max_by_len = (s->L_cap + 255) / 256;  // at least ~256 keys per split
-    if (sp > max_by_len) sp = max_by_len;
-    if (sp < 1) sp = 1;
-    if (sp > 64) sp = 64;
-    pl->splits = sp;
+    pl->splits = pl->splits_full = pl->splits_live = splits_for(target);
+    pl->precise_full = pl->precise_live = kPreciseFrac;
+    if (pl->nt == 256) {
+      // 256-thread workgroups, two per CU: the third round of half the CUs'
+      // workgroups pays where sequences are long, or where dead row passes
+      // (tree_len) leave CUs idle; otherwise exactly two per CU are faster:
+      // splits of up to about 3072 keys, or 544 with tree_len.  Measured in
+      // us, 512 against 768 workgroups (longest split of the 512): without
+      // tree_len 2 x 256 nodes (1088 keys) 52.5 / 64.9, 16 x 64 (544) 38.9 /
+      // 47.7, (2080) 71.7 / 74.9, (4128) 112.8 / 104.0, 4 x 64 (1032) 49.1 /
+      // 57.6, (4104) 110.4 / 100.5; with it 16 x 64 (544) 35.4 / 40.4, (1536)
+      // 59.0 / 63.0, on 8-bit pages 66.5 / 66.0, 4 x 64 (1032) 44.5 / 43.0, on
+      // 8-bit pages 45.8 / 41.5.  Longer splits carry fewer of a row's keys as
+      // hi + lo; half the threshold keeps the error no larger (1.83e-3 against
+      // 1.92e-3 on the first, 1.73e-3 / 1.79e-3 on the 4 x 64) for about 1 %.
+      const int even = splits_for(2 * kTargetBlocks);
+      const long long keys = (s->L_cap + even - 1LL) / even;
+      if (even < pl->splits && keys <= 3072) {
+        pl->splits_full = even;
+        pl->precise_full = kPreciseFrac / 2;
+      }
+      if (even < pl->splits && keys <= 544) {
+        pl->splits_live = even;
+        pl->precise_live = kPreciseFrac / 2;
+      }
+    }
   } else {
     // fp32: 16-row workgroups; the keys are split while workgroups are fewer
     // than CUs and a split keeps at least 512 keys x 64 columns (about 4 us of
@@ -1445,6 +1476,8 @@ bool make_plan(const ptd_attn_shape* s, int T, Plan* pl) {
     const long long items = static_cast<long long>(s->B) * s->Hkv * pl->passes;
     const int max_by_len = static_cast<int>((static_cast<long long>(s->L_cap) * (s->D / 64) + 511) / 512);
     pl->splits = static_cast<int>(std::min<long long>(std::max<long long>(kTargetBlocks / items, 1), std::min(max_by_len, 64)));
+    pl->splits_full = pl->splits_live = pl->splits;
+    pl->precise_full = pl->precise_live = kPreciseFrac;
   }
   if (static_cast<long long>(s->B) * s->Hkv * pl->passes * pl->splits > 0x7FFFFFFFLL) return false;
   // the combine's grid: one workgroup per 8 (D = 128) or 16 (D = 64) rows of a (b, g)
@@ -1539,9 +1572,11 @@ int attention_impl(const void* q, const void* k_cache, const void* v_cache,
   // fp32 inputs: the split is an option, taken where its partials fit the scratch
   if (!pl.mfma && pl.splits > 1 &&
       pl.partial_bytes + mask_need > (noalloc ? PTD_NOALLOC_SCRATCH_BYTES : workspace ? workspace_bytes : 0)) {
-    pl.splits = 1;
+    pl.splits_full = pl.splits_live = 1;
     pl.partial_bytes = 0;
   }
+  // (the workspace holds the larger count's partials either way)
+  pl.splits = tree_len ? pl.splits_live : pl.splits_full;
   const bool build_mask = mask_need > 0 && T > 128;
   const size_t need = pl.partial_bytes + mask_need;
   if (noalloc && need > 0) {  // the fixed scratch array stands in for the workspace
@@ -1590,6 +1625,7 @@ int attention_impl(const void* q, const void* k_cache, const void* v_cache,
   prm.rows_per_pass = pl.rows_per_pass;
   prm.scale = shape->scale > 0.f ? shape->scale : 1.0f / sqrtf(static_cast<float>(shape->D));
   prm.c = prm.scale * kLog2e;
+  prm.precise = tree_len ? pl.precise_live : pl.precise_full;
   prm.out_bf16 = shape->out_dtype == PTD_BF16;
   prm.page_table = page_table;
   prm.page_shift = page_shift;

@@ -662,6 +662,33 @@ def test_attention_tree_keys_at_any_offset(P, T, Hq, Hkv, D):
         assert np.abs(out.cpu().numpy() - ref[sel]).max() <= TOL["bf16"]
 
 
+@pytest.mark.parametrize("B,T,Hkv,kv,cap", [
+    (24, 36, 8, 500, 544),      # two splits, of which a call without tree sizes takes one
+    (24, 36, 8, 500, 3073),     # ... both: the one would be longer than its limit
+    (3, 130, 8, 900, 1400),     # four per sequence instead of five; room past the keys
+    (16, 33, 8, 700, 1088), (16, 33, 8, 700, 1089)])  # with tree sizes: at the limit and past it
+def test_attention_batch_split_counts(P, B, T, Hkv, kv, cap):
+    rng = np.random.default_rng(B + cap)
+    Hq, D = 4 * Hkv, 64
+    kv_len = rng.integers(kv // 4, kv, B).astype(np.int32)
+    kv_len[0], kv_len[1] = kv, 0
+    parent = np.stack([W.tree_uniform(rng, T)[0] for _ in range(B)])
+    q, k, v = (W.f32_to_bf16_bits(rng.standard_normal(s).astype(np.float32))
+               for s in ((B, T, Hq, D), (B, Hkv, cap, D), (B, Hkv, cap, D)))
+    rows = [(0, 0, T - 1), (1, Hq - 1, 0)] + [
+        (int(rng.integers(B)), int(rng.integers(Hq)), int(rng.integers(T))) for _ in range(10)]
+    ref = O.attention_rows(q, k, v, kv_len, parent, 1.0 / np.sqrt(D), rows)
+    for tl in (None, cu(np.full(B, T, np.int32))):
+        st = torch.zeros(1, dtype=torch.int32, device="cuda")
+        out = P.tree_attention(cu(q), cu(k), cu(v), cu(kv_len), cu(parent),
+                               out_dtype=torch.float32, dev_status=st, tree_len=tl)
+        torch.cuda.synchronize()
+        assert st.item() == 0
+        got = out.cpu().numpy()
+        for n, (b, h, i) in enumerate(rows):
+            assert np.abs(got[b, i, h] - ref[n]).max() <= TOL["bf16"], (b, h, i)
+
+
 @pytest.mark.parametrize("T", [20, 130])
 def test_attention_bad_tree_reports(P, T):
     w = W.make_workload(_spec(T=T, kv_len=50), seed=5, logits=False)
