@@ -16,26 +16,27 @@
 //                    of lowest-index children, and breadth-first renumbering
 //                    of the kept forest level by level (ranks counted over
 //                    the level's mask).
-//   k_pool_merge     one workgroup per sequence.  The sequence's hash table
-//                    (token -> tree) is staged in LDS; every draft node's
-//                    token is looked up, the missing tokens get new trees in
-//                    index order of their first occurrence (while there is
-//                    room) and are inserted.  The touched trees are staged in
-//                    LDS with sibling links, up to 64 at a time; thread j
-//                    merges every sub-tree whose root token keys staged tree
-//                    j, the sub-tree's nodes in index order (the trees are
-//                    independent and proceed together).  The appended nodes,
-//                    the trees' node counts, the new slots and the tree count
-//                    are written back (a merge never changes a stored node).
+//   k_pool_merge     several waves per sequence, each merging some of the
+//                    touched trees in registers.  Every draft node's token is
+//                    looked up in the hash table (token -> tree), the missing
+//                    tokens get new trees in index order of their first
+//                    occurrence (while there is room).  A tree takes the
+//                    sub-trees whose root carries its token in index order of
+//                    the roots, a sub-tree's nodes in index order (the trees
+//                    are independent).  The appended nodes and node counts are
+//                    written back (a merge never changes a stored node); the
+//                    last wave to have read the table inserts the new tokens.
 //   k_pool_retrieve  one workgroup of 192 threads per sequence: 64 hash slots
 //                    from the token's home slot in one load, the tree's nodes
 //                    one per thread, breadth-first order by levels.
 //
-// Pool layout per sequence (ptd_pool_bytes): int32 ntrees, padded to 16
-// bytes; int32 slot_key[H]; int32 slot_tree[H] (-1 empty); int32 count[e_max];
+// Pool layout per sequence (ptd_pool_bytes): int32 ntrees, int32
+// arrivals (0 between calls), padded to 16 bytes; int32 slot_key[H]; int32 slot_tree[H] (-1 empty); int32 count[e_max];
 // int2 node[e_max][n_cap] = (token, parent index in the tree; -1 at the root,
 // which is node 0).  H is the power of two >= 2 e_max (at least 64).  Nodes
 // of a tree are stored in insertion order, so a parent precedes its children.
+#include <algorithm>
+
 #include "ptd_common.hpp"
 
 namespace {
@@ -43,10 +44,7 @@ namespace {
 constexpr int kMaxNodes = 128;            // draft nodes per sequence
 constexpr int kMaxCap = kMaxNodes + 1;    // pool tree capacity, root included
 constexpr int kMaxTrees = 2048;           // pool trees per sequence
-constexpr int kMaxSlots = 4096;
-constexpr int kMergeThreads = 256;
-constexpr int kStageTrees = 64;           // pool trees staged in LDS at a time
-constexpr int kStageSlots = kStageTrees * kMaxCap;
+constexpr int kInitThreads = 256;
 constexpr int kRetrieveThreads = 192;     // >= kMaxCap, whole waves
 constexpr int kRW = kRetrieveThreads / PTD_WAVE;
 
@@ -280,332 +278,328 @@ k_step_prune(const int32_t* __restrict__ parent, const int32_t* __restrict__ tok
 // ---------------------------------------------------------------------------
 // pool
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(kMergeThreads) k_pool_init(void* pool, PoolGeom g) {
+__global__ void __launch_bounds__(kInitThreads) k_pool_init(void* pool, PoolGeom g) {
   const int b = blockIdx.x;
   PoolView P = view(pool, g, b);
-  for (int i = threadIdx.x; i < g.H; i += kMergeThreads) {
+  for (int i = threadIdx.x; i < g.H; i += kInitThreads) {
     P.key[i] = 0;
     P.tree[i] = -1;
   }
-  if (threadIdx.x == 0) *P.ntrees = 0;
+  if (threadIdx.x == 0) {
+    P.ntrees[0] = 0;
+    P.ntrees[1] = 0;  // arrivals of a merge's waves
+  }
 }
 
-struct MergeLds {
-  alignas(16) int key[kMaxSlots];
-  alignas(16) int tree[kMaxSlots];
-  // draft nodes
-  int par[kMaxNodes];
-  alignas(16) int tok[kMaxNodes];
-  int firstof[kMaxNodes];  // first node in index order with the same token
-  int newid[kMaxNodes];    // tree id given to a missing token's first node
-  int jof[kMaxNodes];      // index among the touched trees (first nodes)
-  int jump[kMaxNodes];
-  int newslot[kMaxNodes];
-  uint64_t anc[kMaxNodes][2];
-  uint64_t desc[kMaxNodes][2];  // descendants-or-self of each draft node
-  // touched trees, in order of first use
-  int dtree[kMaxNodes], dkey[kMaxNodes], dnew[kMaxNodes];
-  uint64_t gmask[kMaxNodes][2];  // draft nodes whose sub-trees go to each
-  uint64_t wm[2];                // per-wave ballots
-  int ntrees, nd;
-  // staged trees of one batch: node k of staged tree j at j * n_cap + k
-  int cnt[kStageTrees], cnt0[kStageTrees];
-  int ntok[kStageSlots];
-  short npar[kStageSlots], fc[kStageSlots], ns[kStageSlots];
-  short map[kStageTrees][kMaxNodes];  // draft node -> staged node (-1: dropped)
-};
+// Merge.  One wave per share of a sequence's touched pool trees, X waves per
+// sequence, no LDS and no barrier: node 64 x + lane of the draft in slot x of its
+// lane (NW = 1: drafts of up to 64 nodes), node 64 q + lane of the pool tree at
+// hand in register q.  Every wave looks all tokens up and numbers the new trees
+// (the same in each); it then merges the touched trees of its share one after the
+// other, the next one's records loading meanwhile.  A merge step (one node of one
+// sub-tree) finds the child by a ballot over the tree's nodes.  Nobody may change
+// the hash table while another wave still reads it: each wave counts itself in
+// (word 1 of the sequence's header) once its look-ups are done, and the last one
+// inserts the new tokens and sets the counter back.
+// Bound by latency: token, hash and tree loads (three round trips), then about
+// 0.1 us per merge step of a wave.  16 sequences of 64 nodes into 65-node trees:
+// 10.9 us per call; one workgroup per sequence, tables and trees staged in LDS and
+// one thread per tree, took 28.3 (drafts of 96 nodes into 97-node trees 18.0
+// against 47.6).
+constexpr int kTreeRegs = (kMaxCap + PTD_WAVE - 1) / PTD_WAVE;
 
-// index of node v among the nodes whose flag is set, in index order, from
-// the per-wave ballots in wm (threads 0 .. 127)
-__device__ __forceinline__ int rank_below(const uint64_t* wm, int v) {
-  const int w = v >> 6;
-  return (w ? __popcll(wm[0]) : 0) + __popcll(wm[w] & below_mask(v & 63));
+// r[x] of node i (i: per lane; uniform)
+template <int NW>
+__device__ __forceinline__ int node_get(const int (&r)[NW], int i) {
+  int a = __shfl(r[0], i & 63, PTD_WAVE);
+  if constexpr (NW == 2) {
+    const int c = __shfl(r[1], i & 63, PTD_WAVE);
+    a = i >= 64 ? c : a;
+  }
+  return a;
+}
+template <int NW>
+__device__ __forceinline__ int node_read(const int (&r)[NW], int i) {
+  const int a = __builtin_amdgcn_readlane(r[0], i & 63);
+  if constexpr (NW == 1) return a;
+  else return i >= 64 ? __builtin_amdgcn_readlane(r[NW - 1], i & 63) : a;
 }
 
-__global__ void __launch_bounds__(kMergeThreads)
+// lowest node of a set, taken out of it; -1: empty (uniform)
+template <int NW>
+__device__ __forceinline__ int pop_node(uint64_t (&m)[NW]) {
+  if (m[0]) {
+    const int v = __builtin_ctzll(m[0]);
+    m[0] &= m[0] - 1ull;
+    return v;
+  }
+  if (NW == 2 && m[NW - 1]) {
+    const int v = 64 + __builtin_ctzll(m[NW - 1]);
+    m[NW - 1] &= m[NW - 1] - 1ull;
+    return v;
+  }
+  return -1;
+}
+
+template <int NW>
+__global__ void __launch_bounds__(PTD_WAVE)
 k_pool_merge(void* pool, PoolGeom g, const int32_t* __restrict__ parent,
              const int32_t* __restrict__ tokens, const int32_t* __restrict__ tree_len, int T,
-             int32_t* dev_status) {
-  __shared__ MergeLds L;
-  const int b = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const bool nodes = tid < kMaxNodes;  // waves 0 and 1 hold one draft node each
+             int X, int32_t* dev_status) {
+  const int b = static_cast<int>(blockIdx.x) / X, share = static_cast<int>(blockIdx.x) - b * X;
+  const int lane = threadIdx.x;
   PoolView P = view(pool, g, b);
   int n = T;
   if (tree_len) {
     n = tree_len[b];
     n = n < 0 ? 0 : (n > T ? T : n);
   }
-  const bool live = tid < n;
-  bool bad = false;
-  int par = -1, t = 0;
-  if (live) {
-    par = parent[static_cast<size_t>(b) * T + tid];
-    t = tokens[static_cast<size_t>(b) * T + tid];
-    bad = par < -1 || par >= tid;
-    L.par[tid] = par;
-    L.tok[tid] = t;
+  int par[NW], tok[NW];
+  bool live[NW], bad = false;
+#pragma unroll
+  for (int x = 0; x < NW; ++x) {
+    const int v = 64 * x + lane;
+    live[x] = v < n;
+    par[x] = live[x] ? parent[static_cast<size_t>(b) * T + v] : -1;
+    tok[x] = live[x] ? tokens[static_cast<size_t>(b) * T + v] : 0;
+    bad |= par[x] < -1 || par[x] >= v;
   }
-  if (nodes) {
-    L.gmask[tid][0] = 0ull;
-    L.gmask[tid][1] = 0ull;
-    L.desc[tid][0] = 0ull;
-    L.desc[tid][1] = 0ull;
-    L.newslot[tid] = -1;
-  }
-  {  // the hash table in 16-byte chunks, all of a thread's loads in flight
-     // (named registers: arrays here were moved to LDS and scratch)
-    static_assert(kMaxSlots == 16 * kMergeThreads, "four chunks of keys per thread");
-    const int nq = g.H / 4;
-    const int4* gk = reinterpret_cast<const int4*>(P.key);
-    const int4* gt = reinterpret_cast<const int4*>(P.tree);
-    int4* lk = reinterpret_cast<int4*>(L.key);
-    int4* lt = reinterpret_cast<int4*>(L.tree);
-    const int q0 = tid, q1 = tid + kMergeThreads, q2 = tid + 2 * kMergeThreads,
-              q3 = tid + 3 * kMergeThreads;
-    int4 k0, t0, k1, t1, k2, t2, k3, t3;
-    if (q0 < nq) { k0 = gk[q0]; t0 = gt[q0]; }
-    if (q1 < nq) { k1 = gk[q1]; t1 = gt[q1]; }
-    if (q2 < nq) { k2 = gk[q2]; t2 = gt[q2]; }
-    if (q3 < nq) { k3 = gk[q3]; t3 = gt[q3]; }
-    if (q0 < nq) { lk[q0] = k0; lt[q0] = t0; }
-    if (q1 < nq) { lk[q1] = k1; lt[q1] = t1; }
-    if (q2 < nq) { lk[q2] = k2; lt[q2] = t2; }
-    if (q3 < nq) { lk[q3] = k3; lt[q3] = t3; }
-  }
-  if (tid == 0) L.ntrees = min(max(*P.ntrees, 0), g.e_max);
-  if (__syncthreads_or(bad)) {
-    if (tid == 0) ptd::report(dev_status, PTD_ERR_BAD_TREE);
+  const int ntrees0 = min(max(*P.ntrees, 0), g.e_max);
+  if (__any(bad)) {
+    if (share == 0 && lane == 0) ptd::report(dev_status, PTD_ERR_BAD_TREE);
     return;  // the pool is left as it was
   }
-  const int H = g.H, hb = g.hbits;
-  const int ntrees0 = L.ntrees;
 
-  // lookups; the first node (index order) of every token
-  int e = -1, first = tid;
-  if (live) {
-    for (int s = home_slot(t, hb), k = 0; k < H; ++k, s = (s + 1) & (H - 1)) {
-      const int tr = L.tree[s];
-      if (tr < 0) break;
-      if (L.key[s] == t) {
-        e = tr < g.e_max ? tr : -1;  // an id out of range (a pool not initialised) reads as absent
-        break;
+  // look-ups, four slots of every node at a time; the first ones load while the
+  // first node (index order) of every token is found
+  constexpr int kProbe = 4;
+  const int H = g.H;
+  int ptree[NW][kProbe], pkey[NW][kProbe], home[NW];
+  auto probe = [&](int k0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int x = 0; x < NW; ++x)
+#pragma unroll
+      for (int q = 0; q < kProbe; ++q) {
+        const int s = (home[x] + k0 + q) & (H - 1);
+        ptree[x][q] = P.tree[s];
+        pkey[x][q] = P.key[s];
       }
-    }
-    // four tokens per LDS read (the draft tokens start 16-byte aligned)
-    const int4* tk4 = reinterpret_cast<const int4*>(L.tok);
-    for (int u4 = 0; 4 * u4 < tid && first == tid; ++u4) {
-      const int4 q = tk4[u4];
-      const int u = 4 * u4;
-      if (q.w == t && u + 3 < tid) first = u + 3;
-      if (q.z == t && u + 2 < tid) first = u + 2;
-      if (q.y == t && u + 1 < tid) first = u + 1;
-      if (q.x == t) first = u;
-    }
-    L.firstof[tid] = first;
+  };
+#pragma unroll
+  for (int x = 0; x < NW; ++x) home[x] = home_slot(tok[x], g.hbits);
+  probe(0);
+  int first[NW];
+#pragma unroll
+  for (int x = 0; x < NW; ++x) first[x] = 64 * x + lane;
+#pragma unroll 4
+  for (int u = n - 1; u >= 0; --u) {  // downwards: the lowest match stays
+    const int tu = node_read<NW>(tok, u);
+#pragma unroll
+    for (int x = 0; x < NW; ++x) first[x] = tok[x] == tu ? u : first[x];
   }
+  int e[NW];
+  bool open[NW];
+#pragma unroll
+  for (int x = 0; x < NW; ++x) {
+    e[x] = -1;
+    open[x] = live[x];
+  }
+  for (int k0 = 0;;) {
+    bool more = false;
+#pragma unroll
+    for (int x = 0; x < NW; ++x) {
+#pragma unroll
+      for (int q = 0; q < kProbe; ++q) {
+        const int tr = ptree[x][q];
+        const bool hit = tr >= 0 && pkey[x][q] == tok[x];
+        // an id out of range (a pool not initialised) reads as absent
+        if (open[x] && hit) e[x] = tr < g.e_max ? tr : -1;
+        open[x] = open[x] && tr >= 0 && !hit;
+      }
+      more |= open[x];
+    }
+    k0 += kProbe;
+    if (!__any(more) || k0 >= H) break;
+    probe(k0);
+  }
+  // this wave has read the table and the tree count
+  int* arrivals = P.ntrees + 1;
+  asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+  int arrived = 0;
+  if (lane == 0) arrived = atomicAdd(arrivals, 1);
+
   // new trees for the missing tokens, in index order of their first node
-  const bool newfirst = live && e < 0 && first == tid;
-  if (nodes) {
-    const uint64_t bm = __ballot(newfirst);
-    if (lane == 0) L.wm[wave] = bm;
+  int newid[NW];
+  bool newfirst[NW], created[NW];
+  int nnew = 0;
+#pragma unroll
+  for (int x = 0; x < NW; ++x) {
+    newfirst[x] = live[x] && e[x] < 0 && first[x] == 64 * x + lane;
+    const uint64_t m = __ballot(newfirst[x]);
+    const int id = ntrees0 + nnew + __popcll(m & below_mask(lane));
+    newid[x] = newfirst[x] && id < g.e_max ? id : -1;
+    nnew += __popcll(m);
   }
-  __syncthreads();
-  if (newfirst) {
-    const int id = ntrees0 + rank_below(L.wm, tid);
-    L.newid[tid] = id < g.e_max ? id : -1;
+#pragma unroll
+  for (int x = 0; x < NW; ++x) {
+    const int id = node_get<NW>(newid, first[x]);
+    created[x] = live[x] && e[x] < 0 && id >= 0;
+    if (created[x]) e[x] = id;
   }
-  const int nnew = __popcll(L.wm[0]) + __popcll(L.wm[1]);
-  __syncthreads();
-  bool created = false;
-  if (live && e < 0) {
-    e = L.newid[first];
-    created = e >= 0;
+  // touched trees in order of first use, every X-th one this wave's
+  uint64_t mine[NW], isnew[NW];
+  int nd = 0;
+#pragma unroll
+  for (int x = 0; x < NW; ++x) {
+    const bool use = live[x] && e[x] >= 0 && first[x] == 64 * x + lane;
+    const uint64_t m = __ballot(use);
+    const int j = nd + __popcll(m & below_mask(lane));
+    mine[x] = __ballot(use && j % X == share);
+    isnew[x] = __ballot(created[x]);
+    nd += __popcll(m);
   }
-  if (newfirst && e >= 0) {  // insert token -> tree; slots claimed by compare-and-swap
-    for (int s = home_slot(t, hb), k = 0; k < H; ++k, s = (s + 1) & (H - 1)) {
-      if (atomicCAS(&L.tree[s], -1, e) == -1) {
-        L.key[s] = t;
-        L.newslot[tid] = s;
-        break;
-      }
-    }
+  // ancestor-or-self sets by pointer doubling
+  uint64_t anc[NW][NW];
+  int jump[NW];
+#pragma unroll
+  for (int x = 0; x < NW; ++x) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w) anc[x][w] = live[x] && w == x ? 1ull << lane : 0ull;
+    jump[x] = par[x];
   }
-  // touched trees in order of first use (the first node of their token)
-  const bool firstuse = live && e >= 0 && first == tid;
-  if (nodes) {
-    const uint64_t bm = __ballot(firstuse);
-    if (lane == 0) L.wm[wave] = bm;
-  }
-  __syncthreads();
-  if (firstuse) {
-    const int j = rank_below(L.wm, tid);
-    L.jof[tid] = j;
-    L.dtree[j] = e;
-    L.dkey[j] = t;
-    L.dnew[j] = created ? 1 : 0;
-  }
-  if (tid == 0) {
-    L.nd = __popcll(L.wm[0]) + __popcll(L.wm[1]);
-    L.ntrees = min(ntrees0 + nnew, g.e_max);
-  }
-  // ancestor-or-self masks by pointer jumping
-  uint64_t anc0 = (live && wave == 0) ? (1ull << lane) : 0ull;
-  uint64_t anc1 = (live && wave == 1) ? (1ull << lane) : 0ull;
-  int jump = live ? par : -1;
   for (;;) {
-    if (nodes) {
-      L.anc[tid][0] = anc0;
-      L.anc[tid][1] = anc1;
-      L.jump[tid] = jump;
-    }
-    if (!__syncthreads_or(jump >= 0)) break;
-    if (jump >= 0) {
-      anc0 |= L.anc[jump][0];
-      anc1 |= L.anc[jump][1];
-      jump = L.jump[jump];
-    }
-    __syncthreads();
-  }
-  if (live && e >= 0) {
-    const int j = L.jof[first];
-    atomicOr(&L.gmask[j][wave], 1ull << lane);
-  }
-  // descendant-or-self masks: every node sets its bit in the mask of each
-  // node of its ancestor-or-self set
-  if (live) {
-    for (uint64_t m = anc0; m; m &= m - 1ull)
-      atomicOr(reinterpret_cast<unsigned long long*>(&L.desc[__builtin_ctzll(m)][wave]), 1ull << lane);
-    for (uint64_t m = anc1; m; m &= m - 1ull)
-      atomicOr(reinterpret_cast<unsigned long long*>(&L.desc[64 + __builtin_ctzll(m)][wave]), 1ull << lane);
-  }
-  __syncthreads();
-  const int nd = L.nd, n_cap = g.n_cap;
-
-  for (int j0 = 0; j0 < nd; j0 += kStageTrees) {
-    const int nb = min(kStageTrees, nd - j0);
-    // stage the batch's trees (new ones start as a lone root); a thread's
-    // two loads of a pass are issued before either is used
-    {
-      const int total = nb * n_cap;
-      auto load = [&](int i, int2& v, int& c0) {
-        v = make_int2(0, -1);
-        c0 = 0;
-        if (i < total) {
-          const int jl = i / n_cap, k = i - jl * n_cap;
-          if (!L.dnew[j0 + jl]) {
-            const int et = L.dtree[j0 + jl];
-            v = P.node[static_cast<size_t>(et) * n_cap + k];
-            if (k == 0) c0 = P.count[et];
-          }
-        }
-      };
-      auto store = [&](int i, int2 v, int c0) {
-        if (i >= total) return;
-        const int jl = i / n_cap, k = i - jl * n_cap;
-        if (L.dnew[j0 + jl]) {
-          if (k == 0) {
-            L.ntok[i] = L.dkey[j0 + jl];
-            L.npar[i] = -1;
-            L.cnt[jl] = 1;
-          }
-        } else {
-          L.ntok[i] = v.x;
-          L.npar[i] = static_cast<short>(v.y < 0 || v.y >= k ? -1 : v.y);
-          if (k == 0) L.cnt[jl] = min(max(c0, 1), n_cap);
-        }
-        L.fc[i] = -1;
-        L.ns[i] = -1;
-      };
-      constexpr int kInFlight = 8;  // loads of a thread issued before any is used
-      for (int i = tid; i < total; i += kInFlight * kMergeThreads) {
-        int2 v[kInFlight];
-        int c[kInFlight];
+    bool more = false;
 #pragma unroll
-        for (int q = 0; q < kInFlight; ++q) load(i + q * kMergeThreads, v[q], c[q]);
+    for (int x = 0; x < NW; ++x) more |= jump[x] >= 0;
+    if (!__any(more)) break;
+    int lo[NW], hi[NW], nj[NW];
+    uint64_t na[NW][NW];
 #pragma unroll
-        for (int q = 0; q < kInFlight; ++q) store(i + q * kMergeThreads, v[q], c[q]);
+    for (int w = 0; w < NW; ++w) {
+#pragma unroll
+      for (int x = 0; x < NW; ++x) {
+        lo[x] = static_cast<int>(static_cast<uint32_t>(anc[x][w]));
+        hi[x] = static_cast<int>(static_cast<uint32_t>(anc[x][w] >> 32));
+      }
+#pragma unroll
+      for (int x = 0; x < NW; ++x) {
+        const int a = max(jump[x], 0);
+        na[x][w] = static_cast<uint64_t>(static_cast<uint32_t>(node_get<NW>(lo, a))) |
+                   (static_cast<uint64_t>(static_cast<uint32_t>(node_get<NW>(hi, a))) << 32);
       }
     }
-    __syncthreads();
-    // sibling links of the staged nodes, in insertion order: one thread per
-    // staged tree prepends every node to its parent's list, last node first
-    // (the staging left every link at -1)
-    if (tid < nb) {
-      const int base = tid * n_cap, c = L.cnt[tid];
-      L.cnt0[tid] = L.dnew[j0 + tid] ? 0 : c;  // records below cnt0 are unchanged
-      for (int k = c - 1; k >= 1; --k) {
-        const int p = L.npar[base + k];
-        if (p < 0) continue;  // parents precede their children
-        L.ns[base + k] = L.fc[base + p];
-        L.fc[base + p] = static_cast<short>(k);
+#pragma unroll
+    for (int x = 0; x < NW; ++x) nj[x] = node_get<NW>(jump, max(jump[x], 0));
+#pragma unroll
+    for (int x = 0; x < NW; ++x)
+      if (jump[x] >= 0) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) anc[x][w] |= na[x][w];
+        jump[x] = nj[x];
       }
-    }
-    __syncthreads();
+  }
 
-    // thread jl merges every sub-tree keyed by staged tree jl; a sub-tree's
-    // nodes are visited in index order from its descendant mask, so a
-    // node's parent is mapped before the node
-    if (tid < nb) {
-      const int jl = tid, j = j0 + jl, base = jl * n_cap;
-      int cnt = L.cnt[jl];
+  const int n_cap = g.n_cap;
+  int2 rec[kTreeRegs];
+  int rec_cnt = 0;
+  auto is_new = [&](int f) __attribute__((always_inline)) {
+    const uint64_t m0 = isnew[0], m1 = isnew[NW - 1];
+    return (((f >= 64 ? m1 : m0) >> (f & 63)) & 1ull) != 0;
+  };
+  auto load_tree = [&](int f) __attribute__((always_inline)) {
+    const int et = node_read<NW>(e, f);
+    rec_cnt = 0;
 #pragma unroll
-      for (int gw = 0; gw < 2; ++gw)
-        for (uint64_t gm = L.gmask[j][gw]; gm; gm &= gm - 1ull) {  // sub-tree roots, in order
-          const int u = 64 * gw + __builtin_ctzll(gm);
-          L.map[jl][u] = 0;
+    for (int q = 0; q < kTreeRegs; ++q) {
+      const int k = 64 * q + lane;
+      rec[q] = make_int2(0, -1);
+      if (!is_new(f) && k < n_cap) rec[q] = P.node[static_cast<size_t>(et) * n_cap + k];
+    }
+    if (!is_new(f)) rec_cnt = P.count[et];
+  };
+  int f = pop_node<NW>(mine);  // first node of the tree's token
+  if (f >= 0) load_tree(f);
+  while (f >= 0) {
+    const int et = node_read<NW>(e, f);
+    const bool fresh = is_new(f);  // starts as a lone root
+    int cnt = fresh ? 1 : min(max(__builtin_amdgcn_readfirstlane(rec_cnt), 1), n_cap);
+    const int cnt0 = fresh ? 0 : cnt;  // records below cnt0 stay as they are
+    int ptok[kTreeRegs], ppar[kTreeRegs];  // parent -1: the root, or not a node
 #pragma unroll
-          for (int dw = 0; dw < 2; ++dw) {
-            uint64_t m = L.desc[u][dw];
-            if (dw == (u >> 6)) m &= ~below_mask(u & 63) & ~(1ull << (u & 63));
-            else if (dw < (u >> 6)) m = 0ull;
-            for (; m; m &= m - 1ull) {
-              const int c = 64 * dw + __builtin_ctzll(m);
-              const int pnode = L.map[jl][L.par[c]];
-              if (pnode < 0) {
-                L.map[jl][c] = -1;
-                continue;
+    for (int q = 0; q < kTreeRegs; ++q) {
+      const int k = 64 * q + lane;
+      ptok[q] = rec[q].x;
+      ppar[q] = k < cnt && rec[q].y >= 0 && rec[q].y < k ? rec[q].y : -1;
+      if (fresh && k == 0) ptok[q] = node_read<NW>(tok, f);
+    }
+    const int nf = pop_node<NW>(mine);
+    if (nf >= 0) load_tree(nf);
+    // every sub-tree whose root carries the token, in index order; its nodes in
+    // index order too, so that a node's parent is mapped before the node
+    int map[NW];  // draft node -> node of the pool tree (-1: dropped)
+#pragma unroll
+    for (int x = 0; x < NW; ++x) map[x] = -1;
+    uint64_t roots[NW];
+#pragma unroll
+    for (int x = 0; x < NW; ++x) roots[x] = __ballot(live[x] && first[x] == f);
+    for (int u; (u = pop_node<NW>(roots)) >= 0;) {
+      uint64_t sub[NW];
+#pragma unroll
+      for (int x = 0; x < NW; ++x) {
+        if (u == 64 * x + lane) map[x] = 0;
+        const uint64_t a0 = anc[x][0], a1 = anc[x][NW - 1];
+        sub[x] = __ballot(u != 64 * x + lane && (((u >= 64 ? a1 : a0) >> (u & 63)) & 1ull));
+      }
+      for (int c; (c = pop_node<NW>(sub)) >= 0;) {
+        const int pn = node_read<NW>(map, node_read<NW>(par, c));
+        const int tc = node_read<NW>(tok, c);
+        int k = -1;
+        if (pn >= 0) {
+#pragma unroll
+          for (int q = kTreeRegs - 1; q >= 0; --q) {
+            const uint64_t hit = __ballot(ppar[q] == pn && ptok[q] == tc);
+            if (hit) k = 64 * q + __builtin_ctzll(hit);
+          }
+          if (k < 0 && cnt < n_cap) {  // append as the last child of pn
+            k = cnt++;
+#pragma unroll
+            for (int q = 0; q < kTreeRegs; ++q)
+              if (k == 64 * q + lane) {
+                ptok[q] = tc;
+                ppar[q] = pn;
               }
-              const int tc = L.tok[c];
-              int k = L.fc[base + pnode], last = -1;
-              while (k >= 0 && L.ntok[base + k] != tc) {
-                last = k;
-                k = L.ns[base + k];
-              }
-              if (k < 0 && cnt < n_cap) {  // append as the last child of pnode
-                k = cnt++;
-                L.ntok[base + k] = tc;
-                L.npar[base + k] = static_cast<short>(pnode);
-                L.fc[base + k] = -1;
-                L.ns[base + k] = -1;
-                if (last < 0) L.fc[base + pnode] = static_cast<short>(k);
-                else L.ns[base + last] = static_cast<short>(k);
-              }
-              L.map[jl][c] = static_cast<short>(k);  // -1: full, skipped with its sub-tree
-            }
           }
         }
-      L.cnt[jl] = cnt;
+#pragma unroll
+        for (int x = 0; x < NW; ++x)
+          if (c == 64 * x + lane) map[x] = k;  // -1: full, skipped with its sub-tree
+      }
     }
-    __syncthreads();
+    // a merge only appends
+#pragma unroll
+    for (int q = 0; q < kTreeRegs; ++q) {
+      const int k = 64 * q + lane;
+      if (k >= cnt0 && k < cnt) P.node[static_cast<size_t>(et) * n_cap + k] = make_int2(ptok[q], ppar[q]);
+    }
+    if (lane == 0) P.count[et] = cnt;
+    f = nf;
+  }
 
-    // write back
-    for (int i = tid; i < nb * n_cap; i += kMergeThreads) {
-      const int jl = i / n_cap, k = i - jl * n_cap;
-      const int et = L.dtree[j0 + jl];
-      if (k >= L.cnt0[jl] && k < L.cnt[jl])  // a merge only appends
-        P.node[static_cast<size_t>(et) * n_cap + k] = make_int2(L.ntok[i], L.npar[i]);
-      if (k == 0) P.count[et] = L.cnt[jl];
+  if (__builtin_amdgcn_readfirstlane(arrived) != X - 1) return;
+  // last to have read the table: token -> tree, slots claimed by compare-and-swap
+#pragma unroll
+  for (int x = 0; x < NW; ++x)
+    if (newid[x] >= 0) {
+      for (int s = home[x], k = 0; k < H; ++k, s = (s + 1) & (H - 1))
+        if (atomicCAS(&P.tree[s], -1, newid[x]) == -1) {
+          P.key[s] = tok[x];
+          break;
+        }
     }
-    __syncthreads();  // the staged arrays are reused by the next batch
+  if (lane == 0) {
+    *P.ntrees = min(ntrees0 + nnew, g.e_max);
+    atomicExch(arrivals, 0);
   }
-  if (nodes) {
-    const int s = L.newslot[tid];
-    if (s >= 0) {
-      P.key[s] = L.key[s];
-      P.tree[s] = L.tree[s];
-    }
-  }
-  if (tid == 0) *P.ntrees = L.ntrees;
 }
 
 __global__ void __launch_bounds__(kRetrieveThreads)
@@ -718,7 +712,7 @@ extern "C" int ptd_pool_init(void* pool, size_t pool_bytes, int32_t B, int32_t e
   PTD_RETURN_IF(B < 1 || !pool_geom(e_max, n_cap, &g), PTD_ERR_SHAPE);
   PTD_RETURN_IF(pool_bytes < static_cast<size_t>(B) * g.seq_bytes, PTD_ERR_WORKSPACE);
   PTD_RETURN_IF(!ptd_aligned(pool, 256), PTD_ERR_ALIGN);
-  hipLaunchKernelGGL(k_pool_init, dim3(B), dim3(kMergeThreads), 0,
+  hipLaunchKernelGGL(k_pool_init, dim3(B), dim3(kInitThreads), 0,
                      static_cast<hipStream_t>(stream), pool, g);
   return ptd_launch_status();
 }
@@ -732,9 +726,17 @@ extern "C" int ptd_pool_merge(void* pool, size_t pool_bytes, int32_t B, int32_t 
   PTD_RETURN_IF(B < 1 || !pool_geom(e_max, n_cap, &g) || T < 1 || T > kMaxNodes, PTD_ERR_SHAPE);
   PTD_RETURN_IF(pool_bytes < static_cast<size_t>(B) * g.seq_bytes, PTD_ERR_WORKSPACE);
   PTD_RETURN_IF(!ptd_aligned(pool, 256), PTD_ERR_ALIGN);
-  hipLaunchKernelGGL(k_pool_merge, dim3(B), dim3(kMergeThreads), 0,
-                     static_cast<hipStream_t>(stream), pool, g, parent, tokens, tree_len, T,
-                     dev_status);
+  // Two touched trees per wave at most, four where the waves' repeated look-ups
+  // add up (us per call of 64 nodes, two / four: B = 16 10.9 / 12.2, 64 12.8 /
+  // 14.2, 256 26.3 / 20.6; 96 nodes, B = 64 20.3 / 21.8).  At most 2^32 threads.
+  const int per_wave = static_cast<long long>(B) * T <= 8192 ? 2 : 4;
+  const int X = std::max(1, std::min(ptd_cdiv(T, per_wave), (1 << 25) / B));
+  const dim3 grid(static_cast<unsigned>(B) * X);
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  if (T <= PTD_WAVE)
+    hipLaunchKernelGGL(k_pool_merge<1>, grid, dim3(PTD_WAVE), 0, st, pool, g, parent, tokens, tree_len, T, X, dev_status);
+  else
+    hipLaunchKernelGGL(k_pool_merge<2>, grid, dim3(PTD_WAVE), 0, st, pool, g, parent, tokens, tree_len, T, X, dev_status);
   return ptd_launch_status();
 }
 

@@ -192,3 +192,29 @@ def test_pool_merge_deterministic(P):
             res += [t.cpu() for t in gpu.retrieve(cu(np.full(4, key, np.int32)), 32)]
         outs.append(res)
     assert all(torch.equal(a, b) for a, b in zip(*outs))
+
+
+@pytest.mark.parametrize("B,T", [(1, 1), (127, 64), (130, 64), (3, 66), (64, 128), (65, 128)])
+def test_pool_merge_shares_of_a_batch(P, B, T):
+    # two or four touched trees per wave, the last share short or empty; sequence 0
+    # is a chain of one token (one tree takes every sub-tree), sequence 1 of new
+    # tokens only; merged twice, so that the second merge reads what the waves'
+    # last arrival has inserted
+    rng = np.random.default_rng(B + T)
+    par = trees(rng, B, T, "mix")
+    tok = rng.integers(0, 3 * T, (B, T)).astype(np.int32)
+    par[0], tok[0] = W.tree_chain(T)[0], 7
+    if B > 1:
+        tok[1] = np.arange(T)
+    ref, gpu = O.Pool(B, 300, T + 1), P.Pool(B, 300, T + 1)
+    st = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for step in range(2):
+        ref.merge(par, tok)
+        gpu.merge(cu(par), cu(tok), None, st)
+        tok = np.where(rng.random((B, T)) < 0.3, tok + 1, tok).astype(np.int32)
+    torch.cuda.synchronize()
+    assert st.item() == 0
+    for key in list(range(0, 3 * T + 2, 5)) + [7, 8]:
+        last = np.full(B, key, np.int32)
+        for a, c in zip(ref.retrieve(last, T), gpu.retrieve(cu(last), T)):
+            assert np.array_equal(c.cpu().numpy(), a), key
