@@ -9,13 +9,11 @@
 // next step is the pool tree keyed by the last committed token.
 //
 // Draft trees have at most 128 nodes and pool trees at most 129 (their root
-// included), one node per thread:
-//   k_step_prune     one workgroup of 64 or 128 threads per sequence:
-//                    ancestor masks by pointer jumping through LDS, sub-tree
-//                    depths, the new root of every sub-tree along its chain
-//                    of lowest-index children, and breadth-first renumbering
-//                    of the kept forest level by level (ranks counted over
-//                    the level's mask).
+// included):
+//   k_step_prune     one wave per sequence: ancestor sets by pointer doubling,
+//                    sub-tree depths, the new root of every sub-tree along its
+//                    chain of lowest-index children, and breadth-first
+//                    renumbering of the kept forest level by level.
 //   k_pool_merge     several waves per sequence, each merging some of the
 //                    touched trees in registers.  Every draft node's token is
 //                    looked up in the hash table (token -> tree), the missing
@@ -125,21 +123,112 @@ __device__ __forceinline__ int mask_count(const uint64_t* s_m) {
 }
 
 // ---------------------------------------------------------------------------
-// stepping (NW = 1: trees of up to 64 nodes, 2: up to 128)
+// one wave per tree: node 64 x + lane in slot x of its lane (NW = 1: trees of up
+// to 64 nodes, 2: up to 128), node sets as NW words
+// ---------------------------------------------------------------------------
+// r[x] of node i (i: per lane; uniform)
+template <int NW>
+__device__ __forceinline__ int node_get(const int (&r)[NW], int i) {
+  int a = __shfl(r[0], i & 63, PTD_WAVE);
+  if constexpr (NW == 2) {
+    const int c = __shfl(r[1], i & 63, PTD_WAVE);
+    a = i >= 64 ? c : a;
+  }
+  return a;
+}
+template <int NW>
+__device__ __forceinline__ int node_read(const int (&r)[NW], int i) {
+  const int a = __builtin_amdgcn_readlane(r[0], i & 63);
+  if constexpr (NW == 1) return a;
+  else return i >= 64 ? __builtin_amdgcn_readlane(r[NW - 1], i & 63) : a;
+}
+
+// Ancestor-or-self sets (word w of a node's set: nodes 64 w ..) by pointer doubling.
+template <int NW>
+__device__ __forceinline__ void ancestor_sets(const bool (&live)[NW], const int (&par)[NW],
+                                              uint64_t (&anc)[NW][NW]) {
+  const int lane = threadIdx.x & (PTD_WAVE - 1);
+  int jump[NW];
+#pragma unroll
+  for (int x = 0; x < NW; ++x) {
+#pragma unroll
+    for (int w = 0; w < NW; ++w) anc[x][w] = live[x] && w == x ? 1ull << lane : 0ull;
+    jump[x] = par[x];
+  }
+  for (;;) {
+    bool more = false;
+#pragma unroll
+    for (int x = 0; x < NW; ++x) more |= jump[x] >= 0;
+    if (!__any(more)) break;
+    int lo[NW], hi[NW], nj[NW];
+    uint64_t na[NW][NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+#pragma unroll
+      for (int x = 0; x < NW; ++x) {
+        lo[x] = static_cast<int>(static_cast<uint32_t>(anc[x][w]));
+        hi[x] = static_cast<int>(static_cast<uint32_t>(anc[x][w] >> 32));
+      }
+#pragma unroll
+      for (int x = 0; x < NW; ++x) {
+        const int a = max(jump[x], 0);
+        na[x][w] = static_cast<uint64_t>(static_cast<uint32_t>(node_get<NW>(lo, a))) |
+                   (static_cast<uint64_t>(static_cast<uint32_t>(node_get<NW>(hi, a))) << 32);
+      }
+    }
+#pragma unroll
+    for (int x = 0; x < NW; ++x) nj[x] = node_get<NW>(jump, max(jump[x], 0));
+#pragma unroll
+    for (int x = 0; x < NW; ++x)
+      if (jump[x] >= 0) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) anc[x][w] |= na[x][w];
+        jump[x] = nj[x];
+      }
+  }
+}
+
+// Members of the set m below node i.
+template <int NW>
+__device__ __forceinline__ int count_below(const uint64_t (&m)[NW], int i) {
+  if constexpr (NW == 1) return __popcll(m[0] & below_mask(i & 63));
+  else return i < 64 ? __popcll(m[0] & below_mask(i & 63))
+                     : __popcll(m[0]) + __popcll(m[NW - 1] & below_mask(i & 63));
+}
+
+// Exclusive prefix sum over the lanes, and the total: row_shr 1, 2, 4, 8 within
+// each row of 16 lanes, then the rows' totals by row_bcast 15 and 31.
+__device__ __forceinline__ int wave_excl_sum(int c, int* total) {
+  int x = c;
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);
+  *total = __builtin_amdgcn_readlane(x, 63);
+  return x - c;
+}
+
+// ---------------------------------------------------------------------------
+// stepping: one wave per sequence.  Bound by its chain of dependent LDS and
+// shuffle steps: 4.2 us for 16 trees of 64 nodes (11.0 with a thread per node and
+// a barrier at every step, whose level ranks read every member's key).
 // ---------------------------------------------------------------------------
 template <int NW>
-__global__ void __launch_bounds__(PTD_WAVE * NW)
+__global__ void __launch_bounds__(PTD_WAVE)
 k_step_prune(const int32_t* __restrict__ parent, const int32_t* __restrict__ tokens,
              const int32_t* __restrict__ tree_len, int T, int d_max, int T_max,
              int32_t* __restrict__ parent_next, int32_t* __restrict__ tokens_next,
              int32_t* __restrict__ tree_len_next, int32_t* dev_status) {
   constexpr int N = PTD_WAVE * NW;
-  __shared__ uint64_t s_anc[N][NW];
-  __shared__ uint64_t s_U[N + 1][NW];
-  __shared__ uint64_t s_cm[N][NW];
-  __shared__ int s_jump[N], s_h[N], s_fc[N], s_rootof[N], s_out[N], s_key[N];
-  __shared__ uint64_t s_nr[NW], s_keep[NW], s_lvl[NW];
-  const int v = threadIdx.x, lane = v & 63, wv = v >> 6, b = blockIdx.x;
+  __shared__ uint64_t s_cm[N][NW];  // children
+  __shared__ int s_deep[N];         // depth of the deepest node below or at each
+  __shared__ int s_fc[N];           // lowest-index child
+  __shared__ int s_rootof[N];       // new roots: the old root they replace
+  __shared__ int s_out[N];          // new number
+  __shared__ int s_cnt[N];          // by position in a level: children, then first child's number
+  const int lane = threadIdx.x, b = blockIdx.x;
   int n = T;
   if (tree_len) {
     n = tree_len[b];
@@ -147,132 +236,145 @@ k_step_prune(const int32_t* __restrict__ parent, const int32_t* __restrict__ tok
   }
   int32_t* pn = parent_next + static_cast<size_t>(b) * T_max;
   int32_t* tn = tokens_next + static_cast<size_t>(b) * T_max;
-  const bool live = v < n;
-  const int par = live ? parent[static_cast<size_t>(b) * T + v] : -1;
-  const int tok = live ? tokens[static_cast<size_t>(b) * T + v] : -1;
-  if (__syncthreads_or(live && (par < -1 || par >= v))) {
-    if (v == 0) {
+  int par[NW], tok[NW];
+  bool live[NW], bad = false;
+#pragma unroll
+  for (int x = 0; x < NW; ++x) {
+    const int v = 64 * x + lane;
+    const int p = v < T ? parent[static_cast<size_t>(b) * T + v] : -1;
+    tok[x] = v < T ? tokens[static_cast<size_t>(b) * T + v] : -1;
+    live[x] = v < n;
+    par[x] = live[x] ? p : -1;
+    bad |= par[x] < -1 || par[x] >= v;
+    s_deep[v] = 0;
+    s_fc[v] = N;
+    s_rootof[v] = -1;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) s_cm[v][w] = 0ull;
+  }
+  if (__any(bad)) {
+    if (lane == 0) {
       ptd::report(dev_status, PTD_ERR_BAD_TREE);
       tree_len_next[b] = 0;
     }
-    for (int t = v; t < T_max; t += N) {
+    for (int t = lane; t < T_max; t += PTD_WAVE) {
       pn[t] = -1;
       tn[t] = -1;
     }
     return;
   }
-  // ancestor-or-self masks by pointer jumping
-  uint64_t anc[NW];
+  uint64_t anc[NW][NW];
+  ancestor_sets<NW>(live, par, anc);
+  __syncthreads();  // (one wave: orders the LDS accesses)
+  int dep[NW];
 #pragma unroll
-  for (int w = 0; w < NW; ++w) anc[w] = (live && w == wv) ? (1ull << lane) : 0ull;
-  int jump = par;
-  for (;;) {
+  for (int x = 0; x < NW; ++x) {
+    dep[x] = 0;
 #pragma unroll
-    for (int w = 0; w < NW; ++w) s_anc[v][w] = anc[w];
-    s_jump[v] = jump;
-    if (!__syncthreads_or(jump >= 0)) break;
-    if (jump >= 0) {
-#pragma unroll
-      for (int w = 0; w < NW; ++w) anc[w] |= s_anc[jump][w];
-      jump = s_jump[jump];
+    for (int w = 0; w < NW; ++w) dep[x] += __popcll(anc[x][w]);
+    if (par[x] >= 0) {
+      atomicOr(reinterpret_cast<unsigned long long*>(&s_cm[par[x]][x]), 1ull << lane);
+      atomicMin(&s_fc[par[x]], 64 * x + lane);
     }
-    __syncthreads();
-  }
-  int dep = 0;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) dep += __popcll(anc[w]);
-  // depth of the sub-tree under each node: max over its descendants x of
-  // dep(x) - dep(v) + 1.  U[d], the union of the ancestor-or-self sets of the
-  // nodes at depth d, holds exactly the nodes with a descendant at depth d;
-  // v's descendants fill every level from dep(v) down to its deepest one,
-  // so h(v) counts the consecutive levels d >= dep(v) with v in U[d].
-#pragma unroll
-  for (int w = 0; w < NW; ++w) {
-    s_U[v][w] = 0ull;
-    s_cm[v][w] = 0ull;
-    if (v == 0) {
-      s_U[N][w] = 0ull;
-      s_nr[w] = 0ull;
-    }
-  }
-  __syncthreads();
-  if (live) {
 #pragma unroll
     for (int w = 0; w < NW; ++w)
-      if (anc[w]) atomicOr(&s_U[dep][w], static_cast<unsigned long long>(anc[w]));
-    if (par >= 0) atomicOr(&s_cm[par][wv], 1ull << lane);
+      for (uint64_t m = anc[x][w]; m; m &= m - 1ull) atomicMax(&s_deep[64 * w + __builtin_ctzll(m)], dep[x]);
   }
-  __syncthreads();
-  int h = 0;
-  if (live) {
-    int d = dep;  // v itself is in U[dep]; levels examined eight at a time
-    for (bool more = true; more;) {
-      bool in[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) in[q] = d + 1 + q <= N && ((s_U[min(d + 1 + q, N)][wv] >> lane) & 1ull);
-#pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        more &= in[q];
-        d += more ? 1 : 0;
-      }
-    }
-    h = d - dep + 1;
-  }
-  s_h[v] = h;
-  int fc = -1;
-#pragma unroll
-  for (int w = NW - 1; w >= 0; --w)
-    if (s_cm[v][w]) fc = 64 * w + __builtin_ctzll(s_cm[v][w]);
-  s_fc[v] = fc;
   __syncthreads();
   // every old root steps down its lowest-index children while too deep
-  if (live && par < 0) {
-    int x = v;
-    while (s_h[x] > d_max) x = s_fc[x];
-    s_rootof[x] = v;
-    atomicOr(&s_nr[x >> 6], 1ull << (x & 63));
-  }
-  __syncthreads();
-  bool keep = false;
+  uint64_t old_roots[NW], roots[NW], keep[NW];
 #pragma unroll
-  for (int w = 0; w < NW; ++w) keep |= live && (anc[w] & s_nr[w]) != 0ull;
-  const uint64_t kb = __ballot(keep);
-  if (lane == 0) s_keep[wv] = kb;
-  __syncthreads();
-  int nd = 0;  // depth in the kept forest
-#pragma unroll
-  for (int w = 0; w < NW; ++w) nd += __popcll(anc[w] & s_keep[w]);
-  const int kept = mask_count<NW>(s_keep);
-  const bool is_root = keep && nd == 1;
-  // breadth-first numbering: level 1 by the old root they replace, deeper
-  // levels by (parent's number, old index)
-  int outid = -1, ppid = -1, base = 0;
-  for (int L = 1; base < kept && L <= N; ++L) {  // uniform
-    const bool here = keep && nd == L;
-    __syncthreads();  // numbers of level L - 1 written; s_lvl, s_key free
-    const uint64_t lb = __ballot(here);
-    if (lane == 0) s_lvl[wv] = lb;
-    int key = 0;
-    if (here) key = L == 1 ? s_rootof[v] : s_out[par];
-    s_key[v] = key;
-    __syncthreads();
-    if (here) {
-      outid = base + level_rank<NW>(s_lvl, s_key, v, key);
-      ppid = L == 1 ? -1 : key;
-      s_out[v] = outid;
+  for (int x = 0; x < NW; ++x) {
+    const bool root = live[x] && par[x] < 0;
+    old_roots[x] = __ballot(root);
+    if (root) {
+      int v = 64 * x + lane;
+      for (int d = 1; s_deep[v] - d + 1 > d_max; ++d) v = s_fc[v];
+      s_rootof[v] = 64 * x + lane;
     }
-    base += mask_count<NW>(s_lvl);
   }
-  for (int t = v; t < T_max; t += N) {
+  __syncthreads();
+  int rootof[NW], nd[NW];
+#pragma unroll
+  for (int x = 0; x < NW; ++x) {
+    rootof[x] = s_rootof[64 * x + lane];
+    roots[x] = __ballot(rootof[x] >= 0);
+  }
+  bool kept[NW];
+#pragma unroll
+  for (int x = 0; x < NW; ++x) {
+    kept[x] = false;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) kept[x] |= (anc[x][w] & roots[w]) != 0ull;
+    keep[x] = __ballot(kept[x]);
+  }
+  int total = 0, hi = 0;
+#pragma unroll
+  for (int x = 0; x < NW; ++x) {
+    total += __popcll(keep[x]);
+    hi += __popcll(old_roots[x]);  // one new root each
+    nd[x] = 0;  // depth in the kept forest
+#pragma unroll
+    for (int w = 0; w < NW; ++w) nd[x] += __popcll(anc[x][w] & keep[w]);
+  }
+  // breadth-first numbering: level 1 in the order of the old roots, then level by
+  // level the children (all kept) of a node in index order: a level's nodes write
+  // their child counts at their positions, whose prefix sums number the children
+  int out[NW], pout[NW], sib[NW], nch[NW];
+#pragma unroll
+  for (int x = 0; x < NW; ++x) {
+    out[x] = pout[x] = -1;
+    if (rootof[x] >= 0) out[x] = count_below<NW>(old_roots, rootof[x]);
+    uint64_t cm[NW], own[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+      cm[w] = s_cm[max(par[x], 0)][w];
+      own[w] = s_cm[64 * x + lane][w];
+    }
+    sib[x] = count_below<NW>(cm, 64 * x + lane);
+    nch[x] = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) nch[x] += __popcll(own[w]);
+    if (out[x] >= 0) s_out[64 * x + lane] = out[x];
+  }
+  for (int L = 1, lo = 0; hi < total; ++L) {  // uniform; every level has children up to the last
+    const int len = hi - lo;
+#pragma unroll
+    for (int x = 0; x < NW; ++x)
+      if (kept[x] && nd[x] == L) s_cnt[out[x] - lo] = nch[x];
+    __syncthreads();
+    int run = hi;
+#pragma unroll
+    for (int x = 0; x < NW; ++x) {
+      const int pos = 64 * x + lane;
+      int sum;
+      const int e = wave_excl_sum(pos < len ? s_cnt[pos] : 0, &sum);
+      if (pos < len) s_cnt[pos] = run + e;
+      run += sum;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < NW; ++x)
+      if (kept[x] && nd[x] == L + 1) {
+        pout[x] = s_out[par[x]];
+        out[x] = s_cnt[pout[x] - lo] + sib[x];
+        s_out[64 * x + lane] = out[x];
+      }
+    lo = hi;
+    hi = run;
+    __syncthreads();
+  }
+#pragma unroll
+  for (int x = 0; x < NW; ++x)
+    if (kept[x] && out[x] < T_max) {
+      pn[out[x]] = pout[x];
+      tn[out[x]] = tok[x];
+    }
+  for (int t = total + lane; t < T_max; t += PTD_WAVE) {
     pn[t] = -1;
     tn[t] = -1;
   }
-  __syncthreads();
-  if (keep && outid < T_max) {
-    pn[outid] = is_root ? -1 : ppid;
-    tn[outid] = tok;
-  }
-  if (v == 0) tree_len_next[b] = min(kept, T_max);
+  if (lane == 0) tree_len_next[b] = min(total, T_max);
 }
 
 // ---------------------------------------------------------------------------
@@ -307,23 +409,6 @@ __global__ void __launch_bounds__(kInitThreads) k_pool_init(void* pool, PoolGeom
 // one thread per tree, took 28.3 (drafts of 96 nodes into 97-node trees 18.0
 // against 47.6).
 constexpr int kTreeRegs = (kMaxCap + PTD_WAVE - 1) / PTD_WAVE;
-
-// r[x] of node i (i: per lane; uniform)
-template <int NW>
-__device__ __forceinline__ int node_get(const int (&r)[NW], int i) {
-  int a = __shfl(r[0], i & 63, PTD_WAVE);
-  if constexpr (NW == 2) {
-    const int c = __shfl(r[1], i & 63, PTD_WAVE);
-    a = i >= 64 ? c : a;
-  }
-  return a;
-}
-template <int NW>
-__device__ __forceinline__ int node_read(const int (&r)[NW], int i) {
-  const int a = __builtin_amdgcn_readlane(r[0], i & 63);
-  if constexpr (NW == 1) return a;
-  else return i >= 64 ? __builtin_amdgcn_readlane(r[NW - 1], i & 63) : a;
-}
 
 // lowest node of a set, taken out of it; -1: empty (uniform)
 template <int NW>
@@ -458,46 +543,8 @@ k_pool_merge(void* pool, PoolGeom g, const int32_t* __restrict__ parent,
     isnew[x] = __ballot(created[x]);
     nd += __popcll(m);
   }
-  // ancestor-or-self sets by pointer doubling
   uint64_t anc[NW][NW];
-  int jump[NW];
-#pragma unroll
-  for (int x = 0; x < NW; ++x) {
-#pragma unroll
-    for (int w = 0; w < NW; ++w) anc[x][w] = live[x] && w == x ? 1ull << lane : 0ull;
-    jump[x] = par[x];
-  }
-  for (;;) {
-    bool more = false;
-#pragma unroll
-    for (int x = 0; x < NW; ++x) more |= jump[x] >= 0;
-    if (!__any(more)) break;
-    int lo[NW], hi[NW], nj[NW];
-    uint64_t na[NW][NW];
-#pragma unroll
-    for (int w = 0; w < NW; ++w) {
-#pragma unroll
-      for (int x = 0; x < NW; ++x) {
-        lo[x] = static_cast<int>(static_cast<uint32_t>(anc[x][w]));
-        hi[x] = static_cast<int>(static_cast<uint32_t>(anc[x][w] >> 32));
-      }
-#pragma unroll
-      for (int x = 0; x < NW; ++x) {
-        const int a = max(jump[x], 0);
-        na[x][w] = static_cast<uint64_t>(static_cast<uint32_t>(node_get<NW>(lo, a))) |
-                   (static_cast<uint64_t>(static_cast<uint32_t>(node_get<NW>(hi, a))) << 32);
-      }
-    }
-#pragma unroll
-    for (int x = 0; x < NW; ++x) nj[x] = node_get<NW>(jump, max(jump[x], 0));
-#pragma unroll
-    for (int x = 0; x < NW; ++x)
-      if (jump[x] >= 0) {
-#pragma unroll
-        for (int w = 0; w < NW; ++w) anc[x][w] |= na[x][w];
-        jump[x] = nj[x];
-      }
-  }
+  ancestor_sets<NW>(live, par, anc);
 
   const int n_cap = g.n_cap;
   int2 rec[kTreeRegs];
@@ -771,7 +818,7 @@ extern "C" int ptd_step_prune(const int32_t* parent, const int32_t* tokens,
                        static_cast<hipStream_t>(stream), parent, tokens, tree_len, T, d_max, T_max,
                        parent_next, tokens_next, tree_len_next, dev_status);
   else
-    hipLaunchKernelGGL(k_step_prune<2>, dim3(B), dim3(2 * PTD_WAVE), 0,
+    hipLaunchKernelGGL(k_step_prune<2>, dim3(B), dim3(PTD_WAVE), 0,
                        static_cast<hipStream_t>(stream), parent, tokens, tree_len, T, d_max, T_max,
                        parent_next, tokens_next, tree_len_next, dev_status);
   return ptd_launch_status();
