@@ -387,7 +387,7 @@ struct WalkLds {
   double bk[kMaxBlocks];     // its block references
   double wsum[kWalkWaves];
   RowStat st[kStagedStats];  // every row's block statistics, where they fit
-  int nkids, next, depth, nrej, xblk;
+  int first, last, next, depth, nrej, xblk;
   double before, target;
 };
 
@@ -599,48 +599,52 @@ __global__ void __launch_bounds__(kWalkThreads) k_verify_sample(SampleArgs a) {
     const int k = y / kBlock;
     return term64(logit<BF16>(rowp, y), L.bk[k], a.sc) * L.bscale[k];
   };
-  if (wave == 0) {
-    if (lane == 0)
-      for (int j = 0; j < nrej_t; ++j)  // the rejected tokens' terms leave their blocks
-        L.res[L.rej[j] / kBlock] -= L.p[j];
-    // running totals over the blocks (fp64 wave scans, two blocks per lane:
-    // k = lane and k = 64 + lane); the first block with residual mass whose
-    // running total passes the target; if rounding leaves none, the last
-    // block with residual mass
-    const double r0 = lane < a.nblk ? L.res[lane] : 0.0;
-    const double r1 = lane + PTD_WAVE < a.nblk ? L.res[lane + PTD_WAVE] : 0.0;
-    const double i0 = wave_incl_scan_f64(r0);
-    const double t0 = readlane_f64(i0, PTD_WAVE - 1);
-    const double i1 = t0 + wave_incl_scan_f64(r1);
-    const double total = readlane_f64(i1, PTD_WAVE - 1);
-    const double target = a.u_bonus[row0 + r] * total;
-    const uint64_t h0 = __ballot(r0 > 0.0 && i0 > target), h1 = __ballot(r1 > 0.0 && i1 > target);
-    const uint64_t m0 = __ballot(r0 > 0.0), m1 = __ballot(r1 > 0.0);
-    int xb;
-    if (h0 | h1) xb = h0 ? __builtin_ctzll(h0) : PTD_WAVE + __builtin_ctzll(h1);
-    else if (m1 | m0) xb = m1 ? 2 * PTD_WAVE - 1 - __builtin_clzll(m1) : PTD_WAVE - 1 - __builtin_clzll(m0);
-    else xb = -1;
-    // the running total before block xb: the scans' exclusive values (the
-    // shuffles run on every lane; lane 0's results are replaced afterwards)
-    double e0 = shfl_up_f64(i0, 1);
-    double e1 = shfl_up_f64(i1, 1);
-    if (lane == 0) {
-      e0 = 0.0;
-      e1 = t0;
+  if (tid == 0)
+    for (int j = 0; j < nrej_t; ++j)  // the rejected tokens' terms leave their blocks
+      L.res[L.rej[j] / kBlock] -= L.p[j];
+  // (usually one turn: what is left of a block's sum may be the rounding of terms
+  // that all left it, and such a block is passed over)
+  for (;;) {
+    if (wave == 0) {
+      // running totals over the blocks (fp64 wave scans, two blocks per lane:
+      // k = lane and k = 64 + lane); the first block with residual mass whose
+      // running total passes the target; if rounding leaves none, the last
+      // block with residual mass
+      const double r0 = lane < a.nblk ? L.res[lane] : 0.0;
+      const double r1 = lane + PTD_WAVE < a.nblk ? L.res[lane + PTD_WAVE] : 0.0;
+      const double i0 = wave_incl_scan_f64(r0);
+      const double t0 = readlane_f64(i0, PTD_WAVE - 1);
+      const double i1 = t0 + wave_incl_scan_f64(r1);
+      const double total = readlane_f64(i1, PTD_WAVE - 1);
+      const double target = a.u_bonus[row0 + r] * total;
+      const uint64_t h0 = __ballot(r0 > 0.0 && i0 > target), h1 = __ballot(r1 > 0.0 && i1 > target);
+      const uint64_t m0 = __ballot(r0 > 0.0), m1 = __ballot(r1 > 0.0);
+      int xb;
+      if (h0 | h1) xb = h0 ? __builtin_ctzll(h0) : PTD_WAVE + __builtin_ctzll(h1);
+      else if (m1 | m0) xb = m1 ? 2 * PTD_WAVE - 1 - __builtin_clzll(m1) : PTD_WAVE - 1 - __builtin_clzll(m0);
+      else xb = -1;
+      // the running total before block xb: the scans' exclusive values (the
+      // shuffles run on every lane; lane 0's results are replaced afterwards)
+      double e0 = shfl_up_f64(i0, 1);
+      double e1 = shfl_up_f64(i1, 1);
+      if (lane == 0) {
+        e0 = 0.0;
+        e1 = t0;
+      }
+      const int xl = xb < 0 ? 0 : xb & (PTD_WAVE - 1);
+      const double b0 = readlane_f64(e0, xl), b1 = readlane_f64(e1, xl);
+      if (lane == 0) {
+        L.xblk = total > 0.0 ? xb : -1;
+        L.before = xb >= PTD_WAVE ? b1 : b0;
+        L.target = target;
+      }
     }
-    const int xl = xb < 0 ? 0 : xb & (PTD_WAVE - 1);
-    const double b0 = readlane_f64(e0, xl), b1 = readlane_f64(e1, xl);
-    if (lane == 0) {
-      L.xblk = total > 0.0 ? xb : -1;
-      L.before = xb >= PTD_WAVE ? b1 : b0;
-      L.target = target;
+    __syncthreads();
+    const int xb = L.xblk;
+    if (xb < 0) {  // no residual mass: every token was rejected
+      if (tid == 0) ot[L.depth] = -1;
+      break;
     }
-  }
-  __syncthreads();
-  const int xb = L.xblk;
-  if (xb < 0) {  // no residual mass: every token was rejected
-    if (tid == 0) ot[L.depth] = -1;
-  } else {
     // the block's terms, two consecutive entries per thread, in index order
     const int ya = xb * kBlock + 2 * tid, yb = ya + 1;
     const bool in_a = ya < V && !((L.bits[ya >> 5] >> (ya & 31)) & 1u);
@@ -651,28 +655,33 @@ __global__ void __launch_bounds__(kWalkThreads) k_verify_sample(SampleArgs a) {
     double excl = shfl_up_f64(incl, 1);
     if (lane == 0) excl = 0.0;
     if (lane == 63) L.wsum[wave] = incl;
-    if (tid == 0) L.nkids = kWalkThreads;
+    if (tid == 0) {
+      L.first = kWalkThreads;
+      L.last = -1;
+    }
     __syncthreads();
     double start = L.before;
     for (int w = 0; w < wave; ++w) start += L.wsum[w];
     const double target = L.target;
-    if (own > 0.0 && start + incl > target) atomicMin(&L.nkids, tid);
+    // the first thread past the target; if rounding leaves none, the last one with mass
+    const uint64_t mass = __ballot(own > 0.0), past = __ballot(own > 0.0 && start + incl > target);
+    if (lane == 0 && mass) atomicMax(&L.last, wave * PTD_WAVE + PTD_WAVE - 1 - __builtin_clzll(mass));
+    if (lane == 0 && past) atomicMin(&L.first, wave * PTD_WAVE + __builtin_ctzll(past));
     __syncthreads();
-    bool fallback = false;
-    if (L.nkids == kWalkThreads) {  // rounding: the last thread with mass
-      fallback = true;
-      if (tid == 0) L.nkids = -1;
-      __syncthreads();
-      if (own > 0.0) atomicMax(&L.nkids, tid);
-      __syncthreads();
+    const bool fallback = L.first == kWalkThreads;
+    const int pick = fallback ? L.last : L.first;
+    if (pick >= 0) {  // uniform
+      if (tid == pick) {
+        const double cum = start + excl;
+        int x;
+        if (ea > 0.0 && (!fallback && cum + ea > target)) x = ya;
+        else x = eb > 0.0 ? yb : ya;
+        ot[L.depth] = x;
+      }
+      break;
     }
-    if (tid == L.nkids) {
-      const double cum = start + excl;
-      int x;
-      if (ea > 0.0 && (!fallback && cum + ea > target)) x = ya;
-      else x = eb > 0.0 ? yb : ya;
-      ot[L.depth] = x;
-    }
+    if (tid == 0) L.res[xb] = 0.0;
+    __syncthreads();
   }
   const int depth = L.depth;
   for (int i = tid; i <= T; i += kWalkThreads) {

@@ -216,3 +216,72 @@ def test_sample_odd_rows_masks_and_far_logits(P, dtype, V, kind):
     tok = likely_tokens(rng, lf, par, top=min(3, V))
     for ld in (None, V + 3):
         sample_case(P, lg, tok, par, 1.0, rng.random((B, T)), rng.random((B, T + 1)), ld=ld)
+
+
+def low_level(P, lg, tok, par, temp, u1, u2):
+    """The entry point itself on output buffers that hold -7 before the call."""
+    B, T = par.shape
+    V = lg.shape[-1]
+    t = cu(lg.reshape(B * (T + 1), V))
+    al, an, ot = (torch.full(s, -7, dtype=torch.int32, device="cuda") for s in ((B,), (B, T), (B, T + 1)))
+    ws = torch.empty(P.ptd_verify_sample_workspace_bytes(B, T, V), dtype=torch.uint8, device="cuda")
+    code = P.PTD_BF16 if lg.dtype == np.uint16 else P.PTD_F32
+    P.ptd_verify_sample(t, code, V, V, cu(tok), cu(par), None, B, T, temp, cu(u1), cu(u2), al, an, ot,
+                        ws, ws.numel())
+    torch.cuda.synchronize()
+    return al.cpu().numpy(), an.cpu().numpy(), ot.cpu().numpy()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("T", [3, 31])  # one workgroup per block, one wave per block
+@pytest.mark.parametrize("masked,temp", [(-np.inf, 1.0), (-3.3e38, 1.0), (-1.0e4, 1.0), (-np.inf, 0.01)])
+def test_sample_bonus_where_a_block_lost_all_its_mass(P, dtype, T, masked, temp):
+    # block 1 holds the mass of two neighbours, both drafted and rejected; what
+    # rounding leaves of its sum must not draw the bonus (uniforms of 0 and near 1
+    # reach it from either side): that is block 0's or block 3's only entry
+    rng = np.random.default_rng(T)
+    B, V = 64, 8195
+    par = np.full((B, T), 0, np.int32)
+    par[:, :2] = -1
+    y0, y3 = 77, 3 * 2048 + 5
+    x = np.full((B, T + 1, V), masked, np.float32)
+    a = 2048 + 2 * rng.integers(0, 1000, B)
+    base = 3.0 if temp == 1.0 else 20.0  # a reference of 4 or 2885 (outside the fast range)
+    for b in range(B):
+        x[b, 0, a[b]] = base + temp * rng.random()
+        x[b, 0, a[b] + 1] = base + temp * rng.random()
+        x[b, 0, (y0, y3)[b % 2]] = base
+        x[b, 1:, y0] = 0.0
+    lg = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    tok = np.full((B, T), y0 + 1, np.int32)
+    tok[:, 0], tok[:, 1] = a, a + 1
+    u1 = np.full((B, T), 0.999)
+    for u in (0.0, 1.0 - 2.0 ** -53):
+        al, an, ot = low_level(P, lg, tok, par, temp, u1, np.full((B, T + 1), u))
+        assert (al == 0).all() and (an == -1).all()
+        assert np.array_equal(ot[:, 0], np.where(np.arange(B) % 2, y3, y0))
+        assert (ot[:, 1:] == -1).all()
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_sample_every_token_rejected(P, dtype):
+    # the two drafted tokens hold all the mass; the second one is accepted, or
+    # (the uniform within rounding of 1) nothing is left to draw the bonus from
+    rng = np.random.default_rng(12)
+    B, T, V = 64, 2, 5000
+    par = np.full((B, T), -1, np.int32)
+    x = np.full((B, T + 1, V), -np.inf, np.float32)
+    a = 2 * rng.integers(0, 2000, B)
+    x[np.arange(B), 0, a] = 3.0 + rng.random(B)
+    x[np.arange(B), 0, a + 1] = 3.0 + rng.random(B)
+    x[:, 1:, 9] = 0.0
+    lg = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    tok = np.stack([a, a + 1], 1).astype(np.int32)
+    u1 = np.full((B, T), 1.0 - 2.0 ** -53)
+    u2 = rng.random((B, T + 1))
+    al, an, ot = low_level(P, lg, tok, par, 1.0, u1, u2)
+    for b in range(B):
+        if al[b] == 0:
+            assert (ot[b] == -1).all() and (an[b] == -1).all()
+        else:
+            assert al[b] == 1 and ot[b, 1] == 9 and ot[b, 0] == tok[b, an[b, 0]]
