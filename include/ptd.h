@@ -449,8 +449,8 @@ int ptd_kv_commit(void* k_cache, void* v_cache, const int32_t* kv_len,
                   const ptd_attn_shape* shape, int32_t* kv_len_next, int32_t* dev_status,
                   void* stream);
 
-/* Workspace bytes ptd_verify_sample needs: a (maximum, normalizer) pair of
- * doubles per block of 2048 vocabulary entries per logits row, 256-byte
+/* Workspace bytes ptd_verify_sample needs: 16 bytes (largest logit and sum of
+ * terms) per block of 2048 vocabulary entries per logits row, 256-byte
  * rounded (0 on invalid arguments).  The workspace needs no initialisation;
  * calls sharing one must not overlap. */
 size_t ptd_verify_sample_workspace_bytes(int32_t B, int32_t T, int32_t V);
@@ -469,7 +469,8 @@ size_t ptd_verify_sample_workspace_bytes(int32_t B, int32_t T, int32_t V);
  * sum_{y<=x} P'_y > u_bonus[b][row of v] * W, P' being P_v with the rejected
  * tokens removed and W its total (the last token with P'_y > 0 if rounding
  * leaves none; -1 if W = 0).
- *   logits        [B*(T+1)][ld] of dtype, finite; V entries per row
+ *   logits        [B*(T+1)][ld] of dtype, finite, or -inf for masked entries
+ *                 (probability 0); V entries per row
  *   V             1 .. 262144;  ld >= V (elements)
  *   draft_tokens, parent  int32 [B][T];  tree_len int32 [B] or NULL
  *   temperature   finite, > 0
@@ -480,8 +481,8 @@ size_t ptd_verify_sample_workspace_bytes(int32_t B, int32_t T, int32_t V);
  *   workspace     >= ptd_verify_sample_workspace_bytes(B, T, V), 16-byte aligned
  *   B*(T+1)       at most 65535 rows
  * Precision: the normalizer is a fp64 sum of fp32 exponentials taken per
- * block of 2048 entries relative to the block maximum and rescaled to the
- * row maximum (each factor ~1.2e-7 relative, argument rounding compensated);
+ * block of 2048 entries relative to the block's largest (each ~1.2e-7
+ * relative, argument rounding compensated), rescaled exactly to the row's;
  * the examined children's numerators are fp64; the bonus CDF sums the same
  * terms in fp64.  A uniform within ~5e-7 of the probability or cumulative
  * probability it is compared with may decide differently from an exact

@@ -16,15 +16,16 @@
 //   k_block_stats    one wave per (block of 2048 vocabulary entries, logits
 //                    row), four per workgroup (k_block_stats_wg: one
 //                    workgroup per block, for calls with few blocks): the
-//                    block maximum m_b and
-//                    z_b = sum exp((l - m_b) / temperature) over the block,
-//                    each term an fp32 exponential with its argument's
-//                    rounding compensated (~1.2e-7 relative), added in fp64.
+//                    largest logit m_b and z_b = sum 2^(l c - k_b) over the
+//                    block, c = log2(e) / temperature and k_b the integer
+//                    nearest to m_b c; each term an fp32 exponential with its
+//                    argument's rounding compensated (~1.2e-7 relative), added
+//                    in fp64.
 //   k_verify_sample  one workgroup of 1024 threads per sequence.  Each row's
 //                    k = max_b k_b and normalizer z = sum_b z_b 2^(k_b - k)
-//                    (exact scalings) are formed in LDS; the tree, the uniforms and every
-//                    node's probability under its parent's row (numerator in
-//                    fp64) are staged.  Each level of the walk lists the
+//                    (exact scalings) are formed in LDS; the tree, the
+//                    uniforms and every node's probability under its parent's
+//                    row (numerator in fp64) are staged.  Each level of the walk lists the
 //                    current node's children in index order with ballots, and
 //                    one thread takes the accept / reject decisions in order;
 //                    rejected tokens are marked in an LDS bitmap (one bit per
@@ -104,72 +105,109 @@ __device__ __forceinline__ double readlane_f64(double x, int lane) {
   const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(u >> 32), lane);
   return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
 }
-__device__ __forceinline__ double shfl_xor_f64(double x, int d) {
-  const uint64_t u = __double_as_longlong(x);
-  const uint32_t lo = __shfl_xor(static_cast<uint32_t>(u), d, PTD_WAVE);
-  const uint32_t hi = __shfl_xor(static_cast<uint32_t>(u >> 32), d, PTD_WAVE);
-  return __longlong_as_double(static_cast<long long>((static_cast<uint64_t>(hi) << 32) | lo));
-}
 
-// Sum over a block (or row) of 2^(l c) = z 2^k, c = log2(e) / temperature and k
-// an integer within one of the largest l c (powers of two rescale z exactly).
+// A block's largest logit (the type's lowest value at least) and its sum of
+// 2^(l c - k), k = block_ref(m).
 struct RowStat {
-  double k, z;
+  float m, unused;
+  double z;
 };
 
-// c = log2(e) / temperature as an fp64 value and as c_hi + c_lo in fp32
+// c = log2(e) / temperature as an fp64 value and as c_hi + c_lo in fp32; plain: c
+// is far inside the fp32 range.  l_min and d_min: -2000 / c and -200 / c.
 struct Scale {
   double c;
-  float c_hi, c_lo;
+  float c_hi, c_lo, l_min, d_min;
+  bool plain;
 };
 
-// Blocks whose largest |l c| is within kFastRange take the fp32 term below.
 constexpr float kFastRange = 800.0f;
 constexpr float kGrid = 3072.0f;  // 1.5 * 2^11: adding it rounds |y| < 1024 to multiples of 2^-12
-// Integer reference of a block (or of the terms of one) from its largest logit;
-// a block of -inf only gets a finite one, its terms all 0.
+constexpr float kLowest = -3.402823466e38f;
+constexpr float kLn2 = 0.69314718f;
+// Integer reference of a block from its largest logit: powers of two rescale
+// sums between references exactly.
 __device__ __forceinline__ double block_ref(float m, const Scale& sc) {
-  return fmax(rint(static_cast<double>(m) * sc.c), -1.0e300);
+  return rint(static_cast<double>(m) * sc.c);
 }
-__device__ __forceinline__ bool fast_ref(double k) { return fabs(k) <= kFastRange; }
-// 2^(l c - k) in fp32 for |k| <= kFastRange.  l c is rounded to a multiple of
-// 2^-12 by one FMA, so the subtractions of kGrid and of k are exact; the rest e
-// of l c (at most 2^-13, found by two FMAs) enters to first order (second order
-// below 6e-9).  The term is within about one ulp of v_exp_f32 (~1.2e-7 relative)
-// of the exact value; it is 0 far below the reference, and NaN where l c
-// overflows (l = -inf, the type's lowest value): the callers then take
-// exp_term_any.
-__device__ __forceinline__ void exp_parts(float l, float kf, const Scale& sc, float& p, float& e) {
+// How a block's terms are formed (uniform over the block).
+__device__ __forceinline__ bool fast_ref(double k, const Scale& sc) { return sc.plain && fabs(k) <= kFastRange; }
+// l c - k in fp64, the product rounded first: k is the rounded product's integer,
+// and far from 0 the product's rounding error alone exceeds 1.
+__device__ __forceinline__ double scaled(float l, double k, const Scale& sc) {
+#pragma clang fp contract(off)
+  const double lc = static_cast<double>(l) * sc.c;
+  return lc - k;
+}
+// A term as p (1 + e ln 2): p = 2^x in fp32 with e the rest of the exponent, which
+// enters to first order.  The maximum is the one that keeps a NaN.
+//
+// Fast: 2^(l c - k) for |k| <= kFastRange.  l c is rounded to a multiple of 2^-12
+// by one FMA, so the subtractions of kGrid and of k are exact; the rest of l c is
+// at most 2^-13, found by two FMAs (second order below 6e-9).  The term is within
+// about one ulp of v_exp_f32 (~1.2e-7 relative) of the exact value; it is 0 far
+// below the reference.  Where l c overflows (l = -inf, the type's lowest value)
+// it is NaN without the bound l_min, at which the term has long been 0.
+__device__ __forceinline__ void fast_parts(float l, float kf, const Scale& sc, float& p, float& e) {
   const float t = fmaf(l, sc.c_hi, kGrid);
   const float y = t - kGrid;
   e = fmaf(l, sc.c_lo, fmaf(l, sc.c_hi, -y));
   p = __builtin_amdgcn_exp2f(y - kf);
 }
-constexpr float kLn2 = 0.69314718f;
-__device__ __forceinline__ float exp_term(float l, float kf, const Scale& sc) {
-  float p, e;
-  exp_parts(l, kf, sc, p, e);
-  return fmaf(p, e * kLn2, p);
+// Far: 2^((l - m) c) for any other reference (low temperatures, large logits), 0
+// from the bound far_low on.  fp32 logits keep the rounding of l - m (TwoSum).  The
+// difference of bf16 logits is exact unless one of them is 2^16 times the other;
+// rounded, it changes a term 2^x by at most x 2^-25 ln 2, 1.1e-8 of the block's
+// largest.
+__device__ __forceinline__ float far_low(float m, const Scale& sc) {
+  return m + fminf(sc.d_min, -fabsf(m) * 0x1p-22f);  // (below m, however large m is)
 }
-// Sum of two terms, the correction applied once.  k_block_stats is bound by its
-// vector instructions, 11 per entry here (an exponential counted as two) against
-// 19 with (l - m) c, the difference kept in two parts.
-__device__ __forceinline__ float exp_pair(float l0, float l1, float kf, const Scale& sc) {
-  float p0, e0, p1, e1;
-  exp_parts(l0, kf, sc, p0, e0);
-  exp_parts(l1, kf, sc, p1, e1);
+template <bool BF16>
+__device__ __forceinline__ void far_parts(float l, float m, float low, const Scale& sc, float& p, float& e) {
+  l = __builtin_elementwise_maximum(l, low);
+  const float d = l - m;
+  const float x = d * sc.c_hi;
+  e = fmaf(d, sc.c_hi, -x);
+  if constexpr (!BF16) {
+    const float bb = d - l;
+    e = fmaf((l - (d - bb)) + (-m - bb), sc.c_hi, e);
+  }
+  e = fmaf(d, sc.c_lo, e);
+  p = __builtin_amdgcn_exp2f(x);
+}
+__device__ __forceinline__ float one_term(float p, float e) { return fmaf(p * e, kLn2, p); }
+// Sum of two terms, the correction applied once; the same bits as one_term's where
+// the other term is 0, so what is left of a block's sum without its only entry
+// with mass is 0.  k_block_stats is bound by its vector instructions: 11 per
+// entry with fast terms (an exponential counted as two), 12 with their bound,
+// 11 (bf16) or 16 with far terms.  1040 rows x 128256 bf16, whole calls: 57 us;
+// 64 where every block is far (temperature 0.02, logits of deviation 4; 176 with
+// fp64 terms there, 69.5 with far terms of 19 instructions everywhere); 67.5
+// with every third entry masked (202 with fp64 terms).
+__device__ __forceinline__ float two_terms(float p0, float e0, float p1, float e1) {
   return fmaf(fmaf(p1, e1, p0 * e0), kLn2, p0 + p1);
 }
-// The same for any reference (logits or temperatures far from ordinary ones).
-__device__ __noinline__ double exp_term_any(float l, double k, double c) {
-  return exp2(static_cast<double>(l) * c - k);
+// Blocks of the type's lowest values (masks): neighbouring values there are more
+// than 1e10 temperatures apart.
+constexpr float kMasked = -1.0e38f;
+__device__ __forceinline__ float masked_term(float l, float m) { return l == m ? 1.0f : 0.0f; }
+// Temperatures at the ends of the fp32 range.
+__device__ __noinline__ float wide_term(float l, float m, double c) {
+  return static_cast<float>(exp2((static_cast<double>(l) - static_cast<double>(m)) * c));
 }
-__device__ __forceinline__ double term64(float l, double k, const Scale& sc) {
-  if (fast_ref(k)) {
-    const float t = exp_term(l, static_cast<float>(k), sc);
-    if (t == t) return static_cast<double>(t);
-  }
-  return exp_term_any(l, k, sc.c);
+// A term of a block (m, k), and what it is a multiple of: term * scale is
+// 2^(l c - k), for the sums of k_block_stats and for the bonus draw alike.
+template <bool BF16>
+__device__ __forceinline__ float block_term(float l, float m, double k, const Scale& sc) {
+  float p, e;
+  if (fast_ref(k, sc)) fast_parts(__builtin_elementwise_maximum(l, sc.l_min), static_cast<float>(k), sc, p, e);
+  else if (!sc.plain) return wide_term(l, m, sc.c);
+  else if (m < kMasked) return masked_term(l, m);
+  else far_parts<BF16>(l, m, far_low(m, sc), sc, p, e);
+  return one_term(p, e);
+}
+__device__ __forceinline__ double block_scale(float m, double k, const Scale& sc) {
+  return fast_ref(k, sc) ? 1.0 : exp2(scaled(m, k, sc));
 }
 // 2^d for an integer d <= 0 (0 far below the fp64 range)
 __device__ __forceinline__ double pow2i(double d) { return ldexp(1.0, static_cast<int>(fmax(d, -4000.0))); }
@@ -216,12 +254,65 @@ __device__ __forceinline__ float max3(float a, float b, float c) {
   asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
-// Maximum of the entries of a block by plain loads (every lane gets it).
-template <bool BF16>
-__device__ __noinline__ float slow_max(const void* row, int y0, int y1, int lane) {
-  float m = -INFINITY;
-  for (int y = y0 + lane; y < y1; y += PTD_WAVE) m = fmaxf(m, logit<BF16>(row, y));
-  return ptd::wave_max(m);
+// Largest of a lane's chunks and its edge element.
+template <bool BF16, int N>
+__device__ __forceinline__ float chunks_max(const u32x4 (&raw)[N], float le) {
+  constexpr int E = BF16 ? 8 : 4;
+  float m = le;
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    float x[E];
+    chunk_vals<BF16>(raw[j], x);
+#pragma unroll
+    for (int e = 0; e < E; e += 2) m = max3(x[e], x[e + 1], m);
+  }
+  return m;
+}
+// Sum of the terms of a lane's chunks J0 .. J1 - 1 by pairs, added to z.
+template <bool BF16, int J0, int J1, int N, class Pair>
+__device__ __forceinline__ double chunks_sum(const u32x4 (&raw)[N], double z, Pair pair) {
+  constexpr int E = BF16 ? 8 : 4;
+#pragma unroll
+  for (int j = J0; j < J1; ++j) {
+    float x[E];
+    chunk_vals<BF16>(raw[j], x);
+#pragma unroll
+    for (int e = 0; e < E; e += 2)  // pairs added in fp32 (one rounding, 2^-24), then fp64
+      z += static_cast<double>(pair(x[e], x[e + 1]));
+  }
+  return z;
+}
+// Sum of the terms of a lane's chunks and its edge element for any block: masked
+// entries (-inf or overflowing) count 0.
+template <bool BF16, int N>
+__device__ __forceinline__ double chunks_sum_any(const u32x4 (&raw)[N], float le, float m, double k,
+                                                 const Scale& sc) {
+  const double z = static_cast<double>(block_term<BF16>(le, m, k, sc));
+  if (fast_ref(k, sc)) {  // uniform
+    const float kf = static_cast<float>(k);
+    return chunks_sum<BF16, 0, N>(raw, z, [&](float a, float b) {
+      float p0, e0, p1, e1;
+      fast_parts(__builtin_elementwise_maximum(a, sc.l_min), kf, sc, p0, e0);
+      fast_parts(__builtin_elementwise_maximum(b, sc.l_min), kf, sc, p1, e1);
+      return two_terms(p0, e0, p1, e1);
+    });
+  }
+  const double f = block_scale(m, k, sc);
+  if (!sc.plain)
+    return f * chunks_sum<BF16, 0, N>(raw, z, [&](float a, float b) {
+      return wide_term(a, m, sc.c) + wide_term(b, m, sc.c);
+    });
+  if (m < kMasked)
+    return f * chunks_sum<BF16, 0, N>(raw, z, [&](float a, float b) {
+      return masked_term(a, m) + masked_term(b, m);
+    });
+  const float low = far_low(m, sc);
+  return f * chunks_sum<BF16, 0, N>(raw, z, [&](float a, float b) {
+    float p0, e0, p1, e1;
+    far_parts<BF16>(a, m, low, sc, p0, e0);
+    far_parts<BF16>(b, m, low, sc, p1, e1);
+    return two_terms(p0, e0, p1, e1);
+  });
 }
 
 // Block reference, then the block's sum of terms relative to it: one wave per
@@ -258,36 +349,36 @@ k_block_stats(const void* __restrict__ logits, int V, long long ld, int nblk, Sc
     }
   }
   const float le = sp.edge >= 0 ? logit<BF16>(row, sp.edge) : kNone;
-  float m = le;
-#pragma unroll
-  for (int j = 0; j < CPL; ++j) {
-    float x[E];
-    chunk_vals<BF16>(raw[j], x);
-#pragma unroll
-    for (int e = 0; e < E; e += 2) m = max3(x[e], x[e + 1], m);
-  }
-  m = wave_max_uniform(m);
-  if (!(m > kNone)) m = slow_max<BF16>(row, y0, y1, lane);  // uniform; padding taken for an entry
-  const double k = block_ref(m, sc);
+  float m = wave_max_uniform(chunks_max<BF16>(raw, le));
+  double k = block_ref(m, sc);
   double z = __builtin_nan("");
-  if (fast_ref(k)) {  // uniform
+  if (m > kNone && fast_ref(k, sc)) {  // uniform
     const float kf = static_cast<float>(k);
-    z = static_cast<double>(exp_term(le, kf, sc));
-#pragma unroll
-    for (int j = 0; j < CPL; ++j) {
-      float x[E];
-      chunk_vals<BF16>(raw[j], x);
-#pragma unroll
-      for (int e = 0; e < E; e += 2)  // pairs added in fp32 (one rounding, 2^-24), then fp64
-        z += static_cast<double>(exp_pair(x[e], x[e + 1], kf, sc));
-    }
+    const auto pair = [&](float a, float b) {
+      float p0, e0, p1, e1;
+      fast_parts(a, kf, sc, p0, e0);
+      fast_parts(b, kf, sc, p1, e1);
+      return two_terms(p0, e0, p1, e1);
+    };
+    float p, e;
+    fast_parts(le, kf, sc, p, e);
+    z = chunks_sum<BF16, 0, 1>(raw, static_cast<double>(one_term(p, e)), pair);
+    if (!__any(!(z == z))) z = chunks_sum<BF16, 1, CPL>(raw, z, pair);  // (masks are found early)
   }
   if (__any(!(z == z))) {  // uniform: far logits, or masks that overflow l c
-    z = 0.0;
-    for (int y = y0 + lane; y < y1; y += PTD_WAVE) z += exp_term_any(logit<BF16>(row, y), k, sc.c);
+    const uint32_t ninf = BF16 ? 0xFF80FF80u : 0xFF800000u;
+#pragma unroll
+    for (int j = 0; j < CPL; ++j)
+      if (j * PTD_WAVE + lane >= sp.nch) raw[j] = u32x4{ninf, ninf, ninf, ninf};
+    const float lx = sp.edge >= 0 ? le : -INFINITY;
+    if (!(m > kNone)) {  // uniform: padding may have been taken for an entry
+      m = fmaxf(wave_max_uniform(chunks_max<BF16>(raw, lx)), kLowest);
+      k = block_ref(m, sc);
+    }
+    z = chunks_sum_any<BF16>(raw, lx, m, k, sc);
   }
   z = wave_incl_scan_f64(z);
-  if (lane == PTD_WAVE - 1) stats[static_cast<size_t>(r) * nblk + blk] = RowStat{k, z};
+  if (lane == PTD_WAVE - 1) stats[static_cast<size_t>(r) * nblk + blk] = RowStat{m, 0.0f, z};
 }
 
 // The same statistics with one workgroup per (block, row), one or two chunks
@@ -307,54 +398,29 @@ k_block_stats_wg(const void* __restrict__ logits, int V, long long ld, int nblk,
   const char* row = static_cast<const char*>(logits) + static_cast<size_t>(r) * ld * (BF16 ? 2 : 4);
   const int y0 = blk * kBlock, y1 = min(V, y0 + kBlock);
   const BlockSpan<BF16> sp(row, y0, y1, tid);
-  float x[CPT][E];
-  bool have[CPT];
+  const uint32_t ninf = BF16 ? 0xFF80FF80u : 0xFF800000u;
+  u32x4 raw[CPT];
 #pragma unroll
   for (int j = 0; j < CPT; ++j) {
     const int c = tid + j * kStatThreads;
-    have[j] = c < sp.nch;
-    if (have[j]) chunk_vals<BF16>(sp.chunks[c], x[j]);
+    raw[j] = u32x4{ninf, ninf, ninf, ninf};
+    if (c < sp.nch) raw[j] = sp.chunks[c];
   }
   const float le = sp.edge >= 0 ? logit<BF16>(row, sp.edge) : -INFINITY;
-  float m = le;
-#pragma unroll
-  for (int j = 0; j < CPT; ++j)
-    if (have[j])
-#pragma unroll
-      for (int e = 0; e < E; e += 2) m = max3(x[j][e], x[j][e + 1], m);
-  m = wave_max_uniform(m);
+  float m = wave_max_uniform(chunks_max<BF16>(raw, le));
   if (lane == 0) s_max[wave] = m;
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < NW; ++w) m = fmaxf(m, s_max[w]);
-  const double k = block_ref(m, sc);
-  double z = __builtin_nan("");
-  if (fast_ref(k)) {  // uniform
-    const float kf = static_cast<float>(k);
-    z = sp.edge >= 0 ? static_cast<double>(exp_term(le, kf, sc)) : 0.0;
-#pragma unroll
-    for (int j = 0; j < CPT; ++j)
-      if (have[j])
-#pragma unroll
-        for (int e = 0; e < E; e += 2)  // pairs added in fp32 (one rounding, 2^-24), then fp64
-          z += static_cast<double>(exp_pair(x[j][e], x[j][e + 1], kf, sc));
-  }
-  // a wave with far logits or masks redoes its own entries: its chunks and edges
-  if (__any(!(z == z))) {
-    z = sp.edge >= 0 ? exp_term_any(le, k, sc.c) : 0.0;
-#pragma unroll
-    for (int j = 0; j < CPT; ++j)
-      if (have[j])
-#pragma unroll 1
-        for (int e = 0; e < E; ++e) z += exp_term_any(logit<BF16>(sp.chunks + tid + j * kStatThreads, e), k, sc.c);
-  }
-  z = wave_incl_scan_f64(z);
+  m = fmaxf(m, kLowest);
+  // (every entry by its own term: a wave of padding or masks costs no second pass)
+  double z = wave_incl_scan_f64(chunks_sum_any<BF16>(raw, le, m, block_ref(m, sc), sc));
   if (lane == PTD_WAVE - 1) s_sum[wave] = z;
   __syncthreads();
   if (tid == 0) {
     double t = 0.0;
     for (int w = 0; w < NW; ++w) t += s_sum[w];
-    stats[static_cast<size_t>(r) * nblk + blk] = RowStat{k, t};
+    stats[static_cast<size_t>(r) * nblk + blk] = RowStat{m, 0.0f, t};
   }
 }
 
@@ -377,14 +443,14 @@ struct SampleArgs {
 };
 
 struct WalkLds {
-  int par[PTD_MAX_T], tok[PTD_MAX_T], kids[PTD_MAX_T], path[PTD_MAX_T], rej[PTD_MAX_T];
+  int par[PTD_MAX_T], tok[PTD_MAX_T], path[PTD_MAX_T], rej[PTD_MAX_T];
   double p[PTD_MAX_T], u[PTD_MAX_T];
   double rk[PTD_MAX_T + 1];  // row references: the sum of 2^(l c) over row r is
   double rz[PTD_MAX_T + 1];  // rz[r] 2^rk[r]
   uint32_t bits[kMaxVocab / 32];
   double res[kMaxBlocks];    // residual block sums of the terminal's row
-  double bscale[kMaxBlocks]; // 2^(k_b - k) of the terminal's row
-  double bk[kMaxBlocks];     // its block references
+  double bscale[kMaxBlocks]; // what the terms of its blocks are multiples of, over 2^rk
+  float bm[kMaxBlocks];      // its blocks' largest logits
   double wsum[kWalkWaves];
   RowStat st[kStagedStats];  // every row's block statistics, where they fit
   int first, last, next, depth, nrej, xblk;
@@ -395,7 +461,7 @@ struct WalkLds {
 // round trips and barriers, so loads are issued as early as their addresses are
 // known and the block statistics are read once (kept in LDS for the bonus draw
 // when (T + 1) * nblk <= kStagedStats).  16 sequences of 64 nodes, 63 blocks a
-// row: @@ against 16.2 us with one wave per row, a second read of the statistics
+// row: 12.5 against 16.2 us with one wave per row, a second read of the statistics
 // and an LDS look-up and a division per examined child.
 template <bool BF16>
 __global__ void __launch_bounds__(kWalkThreads) k_verify_sample(SampleArgs a) {
@@ -440,23 +506,26 @@ __global__ void __launch_bounds__(kWalkThreads) k_verify_sample(SampleArgs a) {
     }
     for (int h0 = 0; h0 < a.nblk; h0 += kPer * kRowLanes) {
       RowStat st[kAtOnce][kPer];
+      double kb[kAtOnce][kPer];
 #pragma unroll
       for (int j = 0; j < kAtOnce; ++j)
 #pragma unroll
         for (int h = 0; h < kPer; ++h) {
           const int r = r0 + j * kRows, x = h0 + h * kRowLanes + gl;
-          st[j][h] = RowStat{-INFINITY, 0.0};
+          st[j][h] = RowStat{kLowest, 0.0f, 0.0};
           if (r <= T && x < a.nblk) st[j][h] = a.stats[(row0 + r) * a.nblk + x];
         }
 #pragma unroll
       for (int j = 0; j < kAtOnce; ++j) {
-        const double kn = fmax(fmax(fmax(st[j][0].k, st[j][1].k), fmax(st[j][2].k, st[j][3].k)), k[j]);
+#pragma unroll
+        for (int h = 0; h < kPer; ++h) kb[j][h] = block_ref(st[j][h].m, a.sc);
+        const double kn = fmax(fmax(fmax(kb[j][0], kb[j][1]), fmax(kb[j][2], kb[j][3])), k[j]);
         z[j] *= pow2i(k[j] - kn);
         k[j] = kn;
 #pragma unroll
         for (int h = 0; h < kPer; ++h) {
           const int r = r0 + j * kRows, x = h0 + h * kRowLanes + gl;
-          z[j] += st[j][h].z * pow2i(st[j][h].k - kn);
+          z[j] += st[j][h].z * pow2i(kb[j][h] - kn);
           if (staged && r <= T && x < a.nblk) L.st[r * a.nblk + x] = st[j][h];
         }
       }
@@ -498,7 +567,7 @@ __global__ void __launch_bounds__(kWalkThreads) k_verify_sample(SampleArgs a) {
   if (tid < n) {
     const int r = my_par + 1;
     L.p[tid] = (my_tok >= 0 && my_tok < V)
-                   ? exp2(static_cast<double>(my_l) * a.sc.c - L.rk[r]) / L.rz[r]
+                   ? exp2(scaled(my_l, L.rk[r], a.sc)) / L.rz[r]
                    : 0.0;
   }
   if (tid == 0) {
@@ -572,9 +641,9 @@ __global__ void __launch_bounds__(kWalkThreads) k_verify_sample(SampleArgs a) {
   const int v = L.next;
 
   // the bonus token: inverse CDF of the residual distribution of row v + 1.
-  // term(y) = 2^(l_y c - k_b) * 2^(k_b - k) for y in block b, exactly as the
-  // block sums were formed; the residual block sums (block sum less
-  // the rejected terms) locate the block, whose terms are then scanned.
+  // term(y) = 2^(l_y c - k), formed exactly as in the block sums; the residual
+  // block sums (block sum less the rejected terms) locate the block, whose
+  // terms are then scanned.
   const int r = v + 1;
   const double kr = L.rk[r];
   const RowStat* bs = a.stats + (row0 + r) * a.nblk;
@@ -584,20 +653,23 @@ __global__ void __launch_bounds__(kWalkThreads) k_verify_sample(SampleArgs a) {
   const int nrej_t = L.nrej;
   for (int k = tid; k < a.nblk; k += kWalkThreads) {
     const RowStat st = staged ? L.st[r * a.nblk + k] : bs[k];
-    const double f = pow2i(st.k - kr);
-    L.bk[k] = st.k;
-    L.bscale[k] = f;
+    const double kb = block_ref(st.m, a.sc), f = pow2i(kb - kr);
+    L.bm[k] = st.m;
+    L.bscale[k] = block_scale(st.m, kb, a.sc) * f;
     L.res[k] = st.z * f;
   }
   if (tid < nrej_t) {
     const int t = L.rej[tid], k = t / kBlock;
-    const double kb = staged ? L.st[r * a.nblk + k].k : bs[k].k;
-    L.p[tid] = term64(logit<BF16>(rowp, t), kb, a.sc) * pow2i(kb - kr);
+    const float m = staged ? L.st[r * a.nblk + k].m : bs[k].m;
+    const double kb = block_ref(m, a.sc);
+    L.p[tid] = static_cast<double>(block_term<BF16>(logit<BF16>(rowp, t), m, kb, a.sc)) *
+               (block_scale(m, kb, a.sc) * pow2i(kb - kr));
   }
   __syncthreads();
   auto term = [&](int y) -> double {
     const int k = y / kBlock;
-    return term64(logit<BF16>(rowp, y), L.bk[k], a.sc) * L.bscale[k];
+    const float m = L.bm[k];
+    return static_cast<double>(block_term<BF16>(logit<BF16>(rowp, y), m, block_ref(m, a.sc), a.sc)) * L.bscale[k];
   };
   if (tid == 0)
     for (int j = 0; j < nrej_t; ++j)  // the rejected tokens' terms leave their blocks
@@ -723,13 +795,14 @@ extern "C" int ptd_verify_sample(const void* logits, ptd_dtype dtype, int32_t V,
   RowStat* stats = static_cast<RowStat*>(workspace);
   const double c = 1.4426950408889634 / temperature;
   const float c_hi = static_cast<float>(c);
-  const Scale sc{c, c_hi, static_cast<float>(c - static_cast<double>(c_hi))};
+  const Scale sc{c, c_hi, static_cast<float>(c - static_cast<double>(c_hi)), static_cast<float>(-2000.0 / c),
+                 static_cast<float>(-200.0 / c), c >= 1.0e-20 && c <= 1.0e30};
   const int R = B * (T + 1);
   const int nblk = (V + kBlock - 1) / kBlock;
   SampleArgs a{logits, ld, V, T, draft_tokens, parent, tree_len, u_node, u_bonus, stats, nblk,
                sc, accept_len, accept_nodes, out_tokens, dev_status};
   // statistics: one wave per block when the call has many blocks (a batch
-  // of sequences: 1040 rows x 63 blocks, 63.6 against 85 us), else one
+  // of sequences: 1040 rows x 63 blocks, 50.4 against 85 us), else one
   // workgroup per block (a single sequence's 65-97 rows: 0.8 us shorter)
   const bool wave_stats = static_cast<long long>(R) * nblk >= 8192;
   const dim3 sgrid = wave_stats

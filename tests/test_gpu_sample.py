@@ -285,3 +285,88 @@ def test_sample_every_token_rejected(P, dtype):
             assert (ot[b] == -1).all() and (an[b] == -1).all()
         else:
             assert al[b] == 1 and ot[b, 1] == 9 and ot[b, 0] == tok[b, an[b, 0]]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("kind", ["plain", "masked", "far"])
+def test_sample_batch_statistics_odd_rows_masks_and_far_logits(P, dtype, kind):
+    # 2560 rows of 5 blocks: one wave per block.  Rows start at any element
+    # address; a few entries or whole blocks are masked (-inf, the type's lowest
+    # value), or a few blocks lie outside the fp32 fast range
+    rng = np.random.default_rng(len(kind))
+    B, T, V = 40, 63, 8195
+    par = np.stack([W.tree_uniform(rng, T)[0] for _ in range(B)])
+    x = (rng.standard_normal((B, T + 1, V), dtype=np.float32) * 2.0).astype(np.float32)
+    np.put_along_axis(x, np.argmax(x, axis=-1)[..., None], np.max(x, axis=-1, keepdims=True) + 5.0, axis=-1)
+    if kind == "masked":
+        x[::2, :, rng.choice(V, 40, replace=False)] = -np.inf
+        x[1::2, :, rng.choice(V, 40, replace=False)] = np.float32(-3.3e38)
+        x[::3, :, 2048:4096] = -np.inf
+        x[1::3, :, 6144:8195] = -np.inf
+        x[2::3, :, :2048] = np.float32(-3.3e38)
+    if kind == "far":
+        x[::2, :, 2048:4096] += np.float32(700.0)
+        x[1::2, :, 4096:6144] -= np.float32(900.0)
+        x[::5] = x[::5] * np.float32(3.0) - np.float32(1500.0)
+    lg = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    lf = W.bf16_bits_to_f32(lg) if dtype == "bf16" else lg
+    tok = likely_tokens(rng, lf, par)
+    al, _ = sample_case(P, lg, tok, par, 1.0, rng.random((B, T)), rng.random((B, T + 1)), ld=V + 2)
+    assert al.max() >= 2
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,T", [(4, 12), (40, 63)])
+@pytest.mark.parametrize("temp", [0.05, 0.02, 0.01, 1e-3, 1e-32])
+def test_sample_low_temperatures(P, dtype, B, T, temp):
+    # references far from 0; logits a few temperatures apart near the top, so that
+    # the probabilities are not all 0 or 1
+    rng = np.random.default_rng(B)
+    V = 8195
+    par = np.stack([W.tree_uniform(rng, T)[0] for _ in range(B)])
+    x = (rng.standard_normal((B, T + 1, V), dtype=np.float32) * 2.0 + 10.0).astype(np.float32)
+    lg = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    lf = W.bf16_bits_to_f32(lg) if dtype == "bf16" else lg
+    if dtype == "f32" and temp > 1e-6:
+        for j in range(4):
+            y = rng.integers(0, V, (B, T + 1))
+            np.put_along_axis(x, y[..., None], (24.0 - temp * rng.random((B, T + 1)) * 3)[..., None].astype(np.float32),
+                              axis=-1)
+    tok = likely_tokens(rng, lf, par)
+    sample_case(P, lg, tok, par, temp, rng.random((B, T)), rng.random((B, T + 1)))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,T,V", [(1, 96, 128256), (2, 64, 129100), (2, 8, 151936), (1, 5, 262144), (1, 63, 131073)])
+def test_sample_statistics_beyond_the_staged_and_above_64_blocks(P, dtype, B, T, V):
+    # more block statistics than the walk keeps in LDS; more than 64 blocks a row,
+    # the largest entries in the last ones
+    rng = np.random.default_rng(V)
+    par = np.stack([W.tree_uniform(rng, T)[0] for _ in range(B)])
+    x = rng.standard_normal((B, T + 1, V), dtype=np.float32) * np.float32(1.4)
+    hot = rng.integers(max(0, V - 2500), V, (B, T + 1, 6))
+    np.put_along_axis(x, hot, (rng.random((B, T + 1, 6)) * 3 + 11.0).astype(np.float32), axis=-1)
+    x[:, ::3, 100] = 14.5
+    lg = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    lf = W.bf16_bits_to_f32(lg) if dtype == "bf16" else lg
+    tok = likely_tokens(rng, lf, par)
+    sample_case(P, lg, tok, par, 1.0, rng.random((B, T)), rng.random((B, T + 1)))
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("B,T", [(2, 8), (40, 63)])
+def test_sample_whole_rows_masked(P, dtype, B, T):
+    # rows of masks alone: of the type's lowest value (every entry as likely as any
+    # other), with -inf among them, with one entry above
+    rng = np.random.default_rng(T)
+    V = 8195
+    low = np.float32(-3.3895314e38)  # the lowest bf16 value
+    par = np.stack([W.tree_chain(T)[0]] * B)
+    x = np.full((B, T + 1, V), low, np.float32)
+    x[:, 1::3, : V // 2] = -np.inf
+    x[:, 2::3, 4097] = -1.0e30
+    lg = W.f32_to_bf16_bits(x) if dtype == "bf16" else x
+    lf = W.bf16_bits_to_f32(lg) if dtype == "bf16" else lg
+    tok = likely_tokens(rng, lf, par, top=1, p_random=0.5)
+    for temp in (1.0, 0.01, 1e25):
+        sample_case(P, lg, tok, par, temp, rng.random((B, T)) * 1e-4, rng.random((B, T + 1)))
