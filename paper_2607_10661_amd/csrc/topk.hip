@@ -19,6 +19,9 @@
 //                   any element address: the few elements before the slice's
 //                   first 16-byte boundary and after its last whole chunk are
 //                   read one per lane.
+//   k_topk_wave     short rows that are not 16-byte aligned: one wave per row
+//                   with element loads; each lane keeps a sorted list of its
+//                   KMAX best keys in registers.
 // Sorted lists are merged by a butterfly of 6 steps per wave, each merging two
 // sorted lists with a bitonic network.
 //   k_topk_merge    one workgroup per row ranks the slice results by counting
@@ -271,9 +274,8 @@ k_topk_row(const void* __restrict__ logits, int V, long long ld, int slices, int
   const char* sb = rb + static_cast<size_t>(v0) * ES;
   // elements before the slice's first 16-byte boundary (0 for aligned rows).
   // Rows of an odd length, or a view, start anywhere; the chunks stay aligned
-  // loads and only the edges are read by element (65 rows x 32003 bf16: a
-  // wave per row reading elements, as such rows did before, 98 us; now 8.1,
-  // the host call)
+  // loads and only the edges are read by element (65 rows x 32003 bf16, per
+  // call: 5.5 us against 98 for a wave per row reading elements)
   const int head = min(v1 - v0, static_cast<int>((0u - static_cast<uint32_t>(reinterpret_cast<uintptr_t>(sb))) & 15u) / ES);
   const int vb = v0 + head;         // first element of chunk 0
   const int nfull = (v1 - vb) / E;  // whole chunks of the slice (at most NT * NL)
@@ -449,6 +451,31 @@ k_topk_row(const void* __restrict__ logits, int V, long long ld, int slices, int
   else if (lane < KMAX) store_part<BF16>(part, blockIdx.x, KMAX, lane, mine, rb);
 }
 
+// Short unaligned rows: one wave per row, element loads.  A workgroup of
+// k_topk_row costs such a row 1024 threads and several barriers: 16384 rows x 129
+// bf16, k = 4: 15.3 us against 120; 1040 x 513, k = 1: 4.6 against 7.5.
+template <int KMAX, bool BF16>
+__global__ void __launch_bounds__(kThreads)
+k_topk_wave(const void* __restrict__ logits, int R, int V, long long ld, int k,
+            int32_t* __restrict__ argmax, int32_t* __restrict__ topk_idx, float* __restrict__ topk_val) {
+  const int lane = threadIdx.x & 63;
+  const int row = blockIdx.x * (kThreads / PTD_WAVE) + (threadIdx.x >> 6);
+  if (row >= R) return;  // whole wave
+  const char* rb = static_cast<const char*>(logits) + static_cast<size_t>(row) * ld * (BF16 ? 2 : 4);
+  uint64_t l[KMAX];
+#pragma unroll
+  for (int j = 0; j < KMAX; ++j) l[j] = 0;
+  for (int v = lane; v < V; v += PTD_WAVE) {
+    const uint64_t key = make_key(elem_bits<BF16>(rb, v), static_cast<uint32_t>(v));
+    if (key > l[KMAX - 1]) insert<KMAX>(l, key);
+  }
+  wave_merge<KMAX>(l);
+  uint64_t mine = 0;
+#pragma unroll
+  for (int r = 0; r < KMAX; ++r) mine = (lane == r) ? l[r] : mine;
+  emit<BF16>(mine, lane, k, V, rb, row, argmax, topk_idx, topk_val);
+}
+
 // One workgroup per row: the row's slices * KMAX (key, bits) pairs are ranked
 // by counting like the candidates of k_topk_row (empty slots hold key 0,
 // below every element, so they never reach a rank below k <= V).  Beyond
@@ -512,6 +539,7 @@ k_topk_merge(const void* __restrict__ logits, int V, long long ld, int slices, i
 struct TopkPlan {
   int kmax, slices, slice_len;
   int nt, nl;  // k_topk_row: threads per workgroup, 16-byte chunks per lane
+  bool wave;   // k_topk_wave (one slice)
   size_t ws_bytes;
 };
 
@@ -535,10 +563,38 @@ void topk_shape(int R, int V, int E, int* nt, int* nl) {
   }
 }
 
-bool make_topk_plan(int R, int V, int k, int elem_bytes, TopkPlan* p) {
+// Which unaligned rows run one wave per row.  A wave's time grows with the row's
+// elements and, by its insertions, with k; a workgroup's hardly does, but 512 of
+// them run at once.  us, wave / workgroup, bf16, k = 1: 65 rows x 769 4.91 / 4.92, x 1537
+// 6.3 / 4.9; 1040 rows x 1537 6.7 / 7.6, x 2049 7.9 / 7.5; 16384 rows x 2049 29 / 53.  The two meet at
+// about V = 768, 1900 (1040 rows), 2700 (4160 rows), 4000 (16384 rows) for k = 1,
+// 512, 1540, 2600, 4000 for k = 2, none, 700, 1700, 3000 for k = 4, and only from
+// 4096 rows on for larger k.  Rows of fewer than 64 chunks leave k_topk_row without
+// a bound on the k-th best value: 65 rows x 257 bf16, k = 16 17.7 / 36; fp32 rows
+// of about 450 to 640 chunks with one that lists too many candidates for k > 8:
+// 260 rows x 2049, k = 16 34 / 42.
+bool wave_rows(int R, int V, int kmax, int E) {
+  int lg = 0;  // doublings of 256 rows
+  while (lg < 20 && (R >> (lg + 9)) > 0) ++lg;
+  const int big = lg > 3 ? lg - 3 : 0;
+  int limit = 0;
+  switch (kmax) {
+    case 1: limit = 768 + 512 * lg; break;
+    case 2: limit = 512 + 512 * lg; break;
+    case 4: limit = 420 * lg; break;
+    case 8: limit = 448 * big - 192; break;
+    default: limit = E == 8 ? 448 * big - 192 : 64 * big; break;
+  }
+  return V <= (limit < 4096 ? limit : 4096) ||
+         (V < 64 * E && (kmax <= 4 || V >= (kmax == 8 && lg >= 2 ? 128 : 192))) ||
+         (kmax == 16 && E == 4 && lg < 2 && V >= 1800 && V < 2560);
+}
+
+bool make_topk_plan(int R, int V, int k, int elem_bytes, bool aligned, TopkPlan* p) {
   if (R < 1 || V < 1 || k < 1 || k > PTD_MAX_K || k > V) return false;
   p->kmax = k <= 1 ? 1 : k <= 2 ? 2 : k <= 4 ? 4 : k <= 8 ? 8 : 16;
   const int E = 16 / elem_bytes;
+  p->wave = !aligned && wave_rows(R, V, p->kmax, E);
   topk_shape(R, V, E, &p->nt, &p->nl);
   // A slice is at most nt * nl whole chunks (plus, for the last, a partial
   // chunk): rows longer than that are split and merged afterwards.
@@ -557,6 +613,11 @@ bool make_topk_plan(int R, int V, int k, int elem_bytes, TopkPlan* p) {
 template <int KMAX, bool BF16>
 void launch(const TopkPlan& pl, const void* logits, int R, int V, long long ld, int k,
             int32_t* am, int32_t* ti, float* tv, uint64_t* part, hipStream_t st) {
+  if (pl.wave) {
+    hipLaunchKernelGGL((k_topk_wave<KMAX, BF16>), dim3(ptd_cdiv(R, kThreads / PTD_WAVE)), dim3(kThreads), 0,
+                       st, logits, R, V, ld, k, am, ti, tv);
+    return;
+  }
 #define PTD_TOPK_ROW(nt_, nl_)                                                                   \
   if (pl.nt == nt_ && pl.nl == nl_)                                                              \
     hipLaunchKernelGGL((k_topk_row<KMAX, BF16, nt_, nl_>), dim3(R * pl.slices), dim3(nt_), 0, st, \
@@ -585,7 +646,7 @@ void dispatch(const TopkPlan& pl, const void* logits, int R, int V, long long ld
 extern "C" size_t ptd_topk_workspace_bytes(int32_t R, int32_t V, int32_t k) {
   // the dtype is not known here: size for the larger of the bf16 and fp32 plans
   TopkPlan p2, p4;
-  if (!make_topk_plan(R, V, k, 2, &p2) || !make_topk_plan(R, V, k, 4, &p4)) return 0;
+  if (!make_topk_plan(R, V, k, 2, true, &p2) || !make_topk_plan(R, V, k, 4, true, &p4)) return 0;
   return p2.ws_bytes > p4.ws_bytes ? p2.ws_bytes : p4.ws_bytes;
 }
 
@@ -598,8 +659,9 @@ extern "C" int ptd_topk_argmax(const void* logits, ptd_dtype dtype, int32_t R, i
   PTD_RETURN_IF(ld < V, PTD_ERR_SHAPE);
   const size_t es = dtype == PTD_BF16 ? 2 : 4;
   PTD_RETURN_IF(!ptd_aligned(logits, es), PTD_ERR_ALIGN);
+  const bool aligned = ptd_aligned(logits, 16) && (static_cast<size_t>(ld) * es) % 16 == 0;
   TopkPlan pl;
-  PTD_RETURN_IF(!make_topk_plan(R, V, k, static_cast<int>(es), &pl), PTD_ERR_SHAPE);
+  PTD_RETURN_IF(!make_topk_plan(R, V, k, static_cast<int>(es), aligned, &pl), PTD_ERR_SHAPE);
   if (pl.ws_bytes) {
     PTD_RETURN_IF(!workspace || workspace_bytes < pl.ws_bytes, PTD_ERR_WORKSPACE);
     PTD_RETURN_IF(!ptd_aligned(workspace, 8), PTD_ERR_ALIGN);

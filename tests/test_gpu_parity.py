@@ -143,6 +143,37 @@ def test_topk_rows_at_any_address(P, off, V):
         assert np.array_equal(val.cpu().numpy(), np.take_along_axis(arr, order, 1))
 
 
+@pytest.mark.parametrize("bf", [True, False])
+@pytest.mark.parametrize("R,V,k", [
+    (3, 63, 16), (3, 64, 1), (65, 65, 4), (5, 191, 8), (5, 193, 8), (5, 257, 16),  # few chunks
+    (65, 511, 3), (65, 513, 3), (9, 255, 4), (9, 257, 4),
+    (33, 767, 1), (33, 769, 1), (33, 511, 2), (33, 513, 2),                        # few rows
+    (1040, 1791, 1), (1040, 1793, 1), (1040, 839, 4), (1040, 841, 4),              # 1024 rows and more
+    (4100, 255, 7), (4100, 257, 7), (4100, 129, 13), (4100, 259, 13), (1027, 3, 2),
+    (5, 1799, 16), (5, 1801, 16), (5, 2559, 16), (5, 2561, 16)])
+def test_topk_short_rows_at_any_address(P, R, V, k, bf):
+    # a wave per row below the rule's lines, a workgroup per row above them; ties,
+    # -inf, and the last element of a row before the next one's larger values
+    rng = np.random.default_rng(R + V + k)
+    off, ld = 3, V + 2 - (V % 2)
+    x = rng.standard_normal((R, V), dtype=np.float32)
+    x[:, -1:] = 4.0
+    x[1::2, V // 2] = 4.0
+    x[::3, : V // 3] = -np.inf
+    x[::5] = np.round(x[::5])
+    bits = W.f32_to_bf16_bits(x)
+    arr = (bits.astype(np.uint32) << 16).view(np.float32) if bf else x
+    buf = torch.full((off + R * ld,), 1e30, device="cuda",
+                     dtype=torch.bfloat16 if bf else torch.float32)
+    lg = buf[off:].view(R, ld)[:, :V]
+    lg.copy_(cu(arr))
+    am, idx, val = P.topk_argmax(lg, k)
+    order = np.argsort(-arr, axis=1, kind="stable")[:, :k]
+    assert np.array_equal(idx.cpu().numpy(), order)
+    assert np.array_equal(am.cpu().numpy(), order[:, 0])
+    assert np.array_equal(val.cpu().numpy(), np.take_along_axis(arr, order, 1))
+
+
 @pytest.mark.parametrize("k", [1, 4, 16])
 def test_topk_many_ties_at_the_top(P, k):
     # more elements tie with the k-th best than the candidate list holds
