@@ -373,8 +373,8 @@ __global__ void __launch_bounds__(kInitThreads) k_pool_init(void* pool, PoolGeom
 // inserts the new tokens and sets the counter back.
 // Bound by latency: token, hash and tree loads (three round trips), then about
 // 0.1 us per merge step of a wave.  16 sequences of 64 nodes into 65-node trees:
-// 10.9 us per call; one workgroup per sequence, tables and trees staged in LDS and
-// one thread per tree, took 28.3 (drafts of 96 nodes into 97-node trees 18.0
+// 10.3 us per call; one workgroup per sequence, tables and trees staged in LDS and
+// one thread per tree, took 28.3 (drafts of 96 nodes into 97-node trees 17.1
 // against 47.6).
 constexpr int kTreeRegs = (kMaxCap + PTD_WAVE - 1) / PTD_WAVE;
 
@@ -394,12 +394,18 @@ __device__ __forceinline__ int pop_node(uint64_t (&m)[NW]) {
   return -1;
 }
 
-template <int NW>
+// Q: registers per lane that hold a tree's nodes (n_cap <= 64 Q)
+template <int NW, int Q>
 __global__ void __launch_bounds__(PTD_WAVE)
 k_pool_merge(void* pool, PoolGeom g, const int32_t* __restrict__ parent,
              const int32_t* __restrict__ tokens, const int32_t* __restrict__ tree_len, int T,
              int X, int32_t* dev_status) {
-  const int b = static_cast<int>(blockIdx.x) / X, share = static_cast<int>(blockIdx.x) - b * X;
+  // Share by share over the sequences: workgroups go round-robin to the XCDs, so
+  // the first shares, which hold the largest trees, spread over them and start
+  // first (one token in 256 drafts of 128 nodes: 3290 us per call sequence by
+  // sequence, where 32 shares put every first one on the same XCD, now 1163).
+  const int B = static_cast<int>(gridDim.x) / X;
+  const int share = static_cast<int>(blockIdx.x) / B, b = static_cast<int>(blockIdx.x) - share * B;
   const int lane = threadIdx.x;
   PoolView P = view(pool, g, b);
   int n = T;
@@ -515,7 +521,7 @@ k_pool_merge(void* pool, PoolGeom g, const int32_t* __restrict__ parent,
   ancestor_sets<NW>(live, par, anc);
 
   const int n_cap = g.n_cap;
-  int2 rec[kTreeRegs];
+  int2 rec[Q];
   int rec_cnt = 0;
   auto is_new = [&](int f) __attribute__((always_inline)) {
     const uint64_t m0 = isnew[0], m1 = isnew[NW - 1];
@@ -525,7 +531,7 @@ k_pool_merge(void* pool, PoolGeom g, const int32_t* __restrict__ parent,
     const int et = node_read<NW>(e, f);
     rec_cnt = 0;
 #pragma unroll
-    for (int q = 0; q < kTreeRegs; ++q) {
+    for (int q = 0; q < Q; ++q) {
       const int k = 64 * q + lane;
       rec[q] = make_int2(0, -1);
       if (!is_new(f) && k < n_cap) rec[q] = P.node[static_cast<size_t>(et) * n_cap + k];
@@ -539,9 +545,9 @@ k_pool_merge(void* pool, PoolGeom g, const int32_t* __restrict__ parent,
     const bool fresh = is_new(f);  // starts as a lone root
     int cnt = fresh ? 1 : min(max(__builtin_amdgcn_readfirstlane(rec_cnt), 1), n_cap);
     const int cnt0 = fresh ? 0 : cnt;  // records below cnt0 stay as they are
-    int ptok[kTreeRegs], ppar[kTreeRegs];  // parent -1: the root, or not a node
+    int ptok[Q], ppar[Q];  // parent -1: the root, or not a node
 #pragma unroll
-    for (int q = 0; q < kTreeRegs; ++q) {
+    for (int q = 0; q < Q; ++q) {
       const int k = 64 * q + lane;
       ptok[q] = rec[q].x;
       ppar[q] = k < cnt && rec[q].y >= 0 && rec[q].y < k ? rec[q].y : -1;
@@ -565,34 +571,45 @@ k_pool_merge(void* pool, PoolGeom g, const int32_t* __restrict__ parent,
         const uint64_t a0 = anc[x][0], a1 = anc[x][NW - 1];
         sub[x] = __ballot(u != 64 * x + lane && (((u >= 64 ? a1 : a0) >> (u & 63)) & 1ull));
       }
-      for (int c; (c = pop_node<NW>(sub)) >= 0;) {
-        const int pn = node_read<NW>(map, node_read<NW>(par, c));
-        const int tc = node_read<NW>(tok, c);
-        int k = -1;
-        if (pn >= 0) {
+      // The steps hang on each other only through map: a node's token and parent
+      // are read by lane, its match in the tree is found by ballots, and all else
+      // of a step is scalar.  Chains of 128 nodes (63 steps a tree on average),
+      // 256 sequences: 143 us per call against 251 with the node and its
+      // parent's image selected over both words and compared on three registers.
 #pragma unroll
-          for (int q = kTreeRegs - 1; q >= 0; --q) {
-            const uint64_t hit = __ballot(ppar[q] == pn && ptok[q] == tc);
-            if (hit) k = 64 * q + __builtin_ctzll(hit);
-          }
-          if (k < 0 && cnt < n_cap) {  // append as the last child of pn
-            k = cnt++;
+      for (int x = 0; x < NW; ++x)
+        for (uint64_t m = sub[x]; m; m &= m - 1ull) {
+          const int c = __builtin_ctzll(m);  // node 64 x + c
+          const int pc = __builtin_amdgcn_readlane(par[x], c), tc = __builtin_amdgcn_readlane(tok[x], c);
+          int pn = __builtin_amdgcn_readlane(map[0], pc & 63);
+          if constexpr (NW == 2)
+            if (x == 1) {  // (a node of the first word has its parent there)
+              const int hi = __builtin_amdgcn_readlane(map[NW - 1], pc & 63);
+              pn = pc >= 64 ? hi : pn;
+            }
+          int k = -1;  // full, or under a dropped node: skipped with its sub-tree
+          if (pn >= 0) {
+            uint64_t hit[Q];
 #pragma unroll
-            for (int q = 0; q < kTreeRegs; ++q)
-              if (k == 64 * q + lane) {
-                ptok[q] = tc;
-                ppar[q] = pn;
-              }
+            for (int q = 0; q < Q; ++q) hit[q] = __ballot(ppar[q] == pn) & __ballot(ptok[q] == tc);
+#pragma unroll
+            for (int q = Q - 1; q >= 0; --q) k = hit[q] ? 64 * q + __builtin_ctzll(hit[q]) : k;
+            if (k < 0 && cnt < n_cap) {  // append as the last child of pn
+              k = cnt++;
+#pragma unroll
+              for (int q = 0; q < Q; ++q)
+                if (k == 64 * q + lane) {
+                  ptok[q] = tc;
+                  ppar[q] = pn;
+                }
+            }
           }
+          map[x] = lane == c ? k : map[x];
         }
-#pragma unroll
-        for (int x = 0; x < NW; ++x)
-          if (c == 64 * x + lane) map[x] = k;  // -1: full, skipped with its sub-tree
-      }
     }
     // a merge only appends
 #pragma unroll
-    for (int q = 0; q < kTreeRegs; ++q) {
+    for (int q = 0; q < Q; ++q) {
       const int k = 64 * q + lane;
       if (k >= cnt0 && k < cnt) P.node[static_cast<size_t>(et) * n_cap + k] = make_int2(ptok[q], ppar[q]);
     }
@@ -788,16 +805,20 @@ extern "C" int ptd_pool_merge(void* pool, size_t pool_bytes, int32_t B, int32_t 
   PTD_RETURN_IF(pool_bytes < static_cast<size_t>(B) * g.seq_bytes, PTD_ERR_WORKSPACE);
   PTD_RETURN_IF(!ptd_aligned(pool, 256), PTD_ERR_ALIGN);
   // Two touched trees per wave at most, four where the waves' repeated look-ups
-  // add up (us per call of 64 nodes, two / four: B = 16 10.9 / 12.2, 64 12.8 /
-  // 14.2, 256 26.3 / 20.6; 96 nodes, B = 64 20.3 / 21.8).  At most 2^32 threads.
+  // add up (us per call of 64 nodes, two / four: B = 16 10.3 / 11.7, 128 12.0 /
+  // 12.7, 256 19.2 / 14.7; 96 nodes, B = 64 18.5 / 20.8, 128 24.0 / 20.3).  At most
+  // 2^32 threads.
   const int per_wave = static_cast<long long>(B) * T <= 8192 ? 2 : 4;
   const int X = std::max(1, std::min(ptd_cdiv(T, per_wave), (1 << 25) / B));
   const dim3 grid(static_cast<unsigned>(B) * X);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  if (T <= PTD_WAVE)
-    hipLaunchKernelGGL(k_pool_merge<1>, grid, dim3(PTD_WAVE), 0, st, pool, g, parent, tokens, tree_len, T, X, dev_status);
-  else
-    hipLaunchKernelGGL(k_pool_merge<2>, grid, dim3(PTD_WAVE), 0, st, pool, g, parent, tokens, tree_len, T, X, dev_status);
+  const int nw = T <= PTD_WAVE ? 1 : 2, q = ptd_cdiv(n_cap, PTD_WAVE);
+#define PTD_MERGE(nw_, q_)                                                                      \
+  if (nw == nw_ && q == q_)                                                                     \
+    hipLaunchKernelGGL((k_pool_merge<nw_, q_>), grid, dim3(PTD_WAVE), 0, st, pool, g, parent,   \
+                       tokens, tree_len, T, X, dev_status);
+  PTD_MERGE(1, 1) PTD_MERGE(1, 2) PTD_MERGE(1, 3) PTD_MERGE(2, 1) PTD_MERGE(2, 2) PTD_MERGE(2, 3)
+#undef PTD_MERGE
   return ptd_launch_status();
 }
 

@@ -113,8 +113,7 @@ def test_pool_large_trees(P, T, n_cap, V):
 
 
 def test_pool_more_touched_trees_than_staged(P):
-    # about 120 distinct tokens per draft: the touched trees are staged in
-    # two batches
+    # about 120 distinct tokens per draft: 64 waves share the touched trees
     pool_case(P, np.random.default_rng(6), B=2, T=128, V=5000, e_max=2048, n_cap=129, steps=2,
               T_max=128)
 
@@ -218,3 +217,28 @@ def test_pool_merge_shares_of_a_batch(P, B, T):
         last = np.full(B, key, np.int32)
         for a, c in zip(ref.retrieve(last, T), gpu.retrieve(cu(last), T)):
             assert np.array_equal(c.cpu().numpy(), a), key
+
+
+@pytest.mark.parametrize("T", [5, 64, 65, 128])
+@pytest.mark.parametrize("n_cap", [1, 2, 63, 64, 65, 127, 128, 129])
+def test_pool_merge_register_counts(P, T, n_cap):
+    # one, two or three registers of tree nodes, one or two words of draft nodes;
+    # trees that fill exactly, a node below and a node above a register's 64
+    # lanes: chains (a parent in the other word), stars, one token throughout
+    rng = np.random.default_rng(T * 200 + n_cap)
+    B, V = 5, 20
+    ref, gpu = O.Pool(B, 64, n_cap), P.Pool(B, 64, n_cap)
+    for step in range(3):
+        par = trees(rng, B, T, "mix")
+        tok = rng.integers(0, V, (B, T)).astype(np.int32)
+        tok[1, : T // 2] = 3  # a chain's nodes in one tree
+        par[4], tok[4] = W.tree_chain(T)[0], step
+        st = torch.zeros(1, dtype=torch.int32, device="cuda")
+        ref.merge(par, tok)
+        gpu.merge(cu(par), cu(tok), None, st)
+        torch.cuda.synchronize()
+        assert st.item() == 0
+        for key in range(V):
+            last = np.full(B, key, np.int32)
+            for a, c in zip(ref.retrieve(last, 128), gpu.retrieve(cu(last), 128)):
+                assert np.array_equal(c.cpu().numpy(), a), (step, key)
