@@ -1575,8 +1575,10 @@ int attention_impl(const void* q, const void* k_cache, const void* v_cache,
   if (!pl.mfma) PTD_RETURN_IF(shape->Hkv > 65535 || shape->B > 65535, PTD_ERR_SHAPE);
   const size_t mask_need = pl.needs_mask && !mask ? pl.mask_bytes : 0;
   // fp32 inputs: the split is an option, taken where its partials fit the scratch
-  if (!pl.mfma && pl.splits > 1 &&
-      pl.partial_bytes + mask_need > (noalloc ? PTD_NOALLOC_SCRATCH_BYTES : workspace ? workspace_bytes : 0)) {
+  // (a workspace that is not aligned for them counts as none)
+  const size_t room = noalloc ? PTD_NOALLOC_SCRATCH_BYTES
+                              : workspace && ptd_aligned(workspace, 256) ? workspace_bytes : 0;
+  if (!pl.mfma && pl.splits > 1 && pl.partial_bytes + mask_need > room) {
     pl.splits_full = pl.splits_live = 1;
     pl.partial_bytes = 0;
   }

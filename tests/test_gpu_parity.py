@@ -568,6 +568,27 @@ def test_attention_fp32_tiles_splits_and_padding(P, D, Hq, Hkv, T, kv):
     assert np.abs(got.cpu().numpy() - r2).max() <= TOL["f32"]
 
 
+@pytest.mark.parametrize("off", [0, 8, 64, 255])
+def test_attention_fp32_given_masks_any_workspace(P, off):
+    # with the masks given, fp32 attention needs no workspace: one at any address,
+    # and none, is as good (the keys are split only where it can hold the partials)
+    w = W.make_workload(_spec(dtype="f32", D=128, Hq=2, Hkv=2, T=16, B=1, kv_len=[2000]), seed=off, logits=False)
+    q, kc, vc, kvl, par = cu(w.q), cu(w.k_cache), cu(w.v_cache), cu(w.kv_len), cu(w.parent)
+    ref = O.tree_attention(w.q, w.k_cache, w.v_cache, w.kv_len, w.parent, w.scale)
+    shape = P.AttnShape(1, 2, 2, 128, kc.shape[2], P.PTD_F32, P.PTD_F32, 0.0)
+    mask = P.tree_mask(par)[0]
+    need = P.ptd_tree_attention_workspace_bytes(shape, 16)
+    assert need > 16 * 8 + 256  # the plan splits the keys
+    buf = torch.empty(need + 512, dtype=torch.uint8, device="cuda")
+    for ws in (buf[off:off + need], None):
+        out = torch.full_like(q, float("nan"))
+        st = status_buf()
+        P.ptd_tree_attention(q, kc, vc, kvl, par, 16, out, shape, mask, ws, 0 if ws is None else need, st)
+        torch.cuda.synchronize()
+        assert st.item() == 0
+        assert np.abs(out.cpu().numpy() - ref).max() <= TOL["f32"]
+
+
 def test_attention_tiny_config(P):
     w = W.make_workload("tiny", logits=False)
     ref = O.tree_attention(w.q, w.k_cache, w.v_cache, w.kv_len, w.parent, w.scale)
