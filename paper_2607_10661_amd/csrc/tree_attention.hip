@@ -96,7 +96,7 @@ __device__ inline int live_nodes(const AttnParams& p, int b) {
   return p.tree_len ? min(max(p.tree_len[b], 0), p.T) : p.T;
 }
 
-__device__ inline void logical_block(int nblocks, int npairs, bool by_size, int& id) {
+__device__ inline void logical_block(int bid, int nblocks, int npairs, bool by_size, int& id) {
   // Workgroups are dealt round-robin over the 8 XCDs (block i to XCD i mod 8)
   // and each XCD runs its share in block order.  The items of one (b, g) pair
   // (its row passes and KV splits) share keys and query rows, so they stay on
@@ -105,7 +105,6 @@ __device__ inline void logical_block(int nblocks, int npairs, bool by_size, int&
   // XCD q mod 8), so every XCD gets a like share of long and short sequences
   // and runs its own largest first; otherwise each XCD takes a contiguous
   // range of pairs.
-  const int bid = blockIdx.x;
   if (by_size && (npairs & 7) == 0 && (nblocks & 7) == 0) {
     const int ips = nblocks / npairs;  // items per pair
     const int x = bid & 7, j = bid >> 3;
@@ -243,7 +242,7 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   // of 512-8192 keys, decode-sized calls 99.7 against 101.4).
   const bool by_size = p.B > 1 && p.B <= PTD_WAVE;
   int id;
-  logical_block(gridDim.x, p.B * p.Hkv, by_size, id);
+  logical_block(blockIdx.x, gridDim.x, p.B * p.Hkv, by_size, id);
   const int split = id % p.splits;
   int rest = id / p.splits;
   const int pass = rest % p.passes;
@@ -1219,7 +1218,9 @@ __global__ void __launch_bounds__(kF32Threads, 2) k_attn_f32(AttnParams p) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l16 = lane & 15, l4 = lane >> 4;
   int id;
-  logical_block(gridDim.x, p.B * p.Hkv, false, id);
+  // (a grid of three dimensions: one of them holds fewer than 2^32 threads)
+  const int bid = blockIdx.x + gridDim.x * (blockIdx.y + gridDim.y * blockIdx.z);
+  logical_block(bid, p.B * p.Hkv * p.passes * p.splits, p.B * p.Hkv, false, id);
   const int split = id % p.splits;
   int rest = id / p.splits;
   const int r0 = (rest % p.passes) * kF32Rows;
@@ -1652,7 +1653,7 @@ int attention_impl(const void* q, const void* k_cache, const void* v_cache,
     if (page_table) launch(std::true_type{});
     else launch(std::false_type{});
   } else {
-    const dim3 grid(prm.B * prm.Hkv * pl.passes * pl.splits);
+    const dim3 grid(pl.passes * pl.splits, prm.Hkv, prm.B);
     if (shape->D == 128) hipLaunchKernelGGL(k_attn_f32<128>, grid, dim3(kF32Threads), 0, st, prm);
     else hipLaunchKernelGGL(k_attn_f32<64>, grid, dim3(kF32Threads), 0, st, prm);
   }

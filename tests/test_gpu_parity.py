@@ -589,6 +589,22 @@ def test_attention_fp32_given_masks_any_workspace(P, off):
         assert np.abs(out.cpu().numpy() - ref).max() <= TOL["f32"]
 
 
+def test_attention_fp32_more_workgroups_than_one_dimension_holds(P):
+    # 65535 sequences x 129 heads: 8.45 M workgroups of 512 threads, more than 2^32
+    # threads.  One key per row: its value is the output
+    B, H, D = 65535, 129, 64
+    q = torch.ones((B, 1, H, D), device="cuda")
+    v = torch.arange(B * H, device="cuda", dtype=torch.float32).view(B, H, 1, 1).expand(B, H, 1, D).contiguous()
+    v += torch.arange(D, device="cuda") * 0.0078125
+    kvl = torch.zeros(B, dtype=torch.int32, device="cuda")
+    par = torch.full((B, 1), -1, dtype=torch.int32, device="cuda")
+    st = status_buf()
+    out = P.tree_attention(q, v, v, kvl, par, scale=1e-9, dev_status=st)
+    torch.cuda.synchronize()
+    assert st.item() == 0
+    assert torch.equal(out, v.view(B, 1, H, D))
+
+
 def test_attention_tiny_config(P):
     w = W.make_workload("tiny", logits=False)
     ref = O.tree_attention(w.q, w.k_cache, w.v_cache, w.kv_len, w.parent, w.scale)
