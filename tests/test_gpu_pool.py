@@ -242,3 +242,37 @@ def test_pool_merge_register_counts(P, T, n_cap):
             last = np.full(B, key, np.int32)
             for a, c in zip(ref.retrieve(last, 128), gpu.retrieve(cu(last), 128)):
                 assert np.array_equal(c.cpu().numpy(), a), (step, key)
+
+
+@pytest.mark.parametrize("T", [2, 63, 64, 65, 127, 128])
+def test_step_prune_depths_by_first_children(P, T):
+    # the deepest node lies below a first child, a later child, a later root; many
+    # leaves at the deepest level under parents of their own; chains
+    rng = np.random.default_rng(T)
+    forests = [W.tree_chain(T)[0]]
+    for stem in (1, T // 3, T - 2):
+        p = list(range(-1, max(1, stem) - 1))  # a stem, then arms of two nodes each
+        while len(p) < T:
+            p.append(max(1, stem) - 1 if (len(p) - stem) % 2 == 0 else len(p) - 1)
+        forests.append(np.asarray(p[:T], np.int32))
+    p = [-1, 0, 0] + [2] * T  # the first child a leaf, all depth below the second
+    for i in range(4, T):
+        p[i] = i - 1
+    forests.append(np.asarray(p[:T], np.int32))
+    p = [-1] * T              # roots of which the last ones carry chains
+    for i in range(T // 2, T):
+        p[i] = i - 3 if i - 3 >= 0 else -1
+    forests.append(np.asarray(p, np.int32))
+    forests += [W.tree_uniform(rng, T)[0] for _ in range(4)]
+    par = np.stack(forests)
+    tok = rng.integers(0, 99, par.shape).astype(np.int32)
+    tl = rng.integers(0, T + 1, len(par)).astype(np.int32)
+    for d_max in (1, 2, 3, T // 2 + 1, T - 1, T, 1000):
+        for tree_len in (None, tl):
+            r = O.step_prune(par, tok, max(1, d_max), 128, tree_len)
+            st = torch.zeros(1, dtype=torch.int32, device="cuda")
+            g = P.step_prune(cu(par), cu(tok), max(1, d_max), 128, None if tree_len is None else cu(tree_len), st)
+            torch.cuda.synchronize()
+            assert st.item() == 0
+            for a, c in zip(r, g):
+                assert np.array_equal(c.cpu().numpy(), a), d_max
