@@ -95,14 +95,6 @@ __device__ __forceinline__ void dma4(const void* gptr, uint32_t lds) {
       : "memory");
 }
 
-// 4-byte global load into a VGPR from inline asm (not tracked by the
-// compiler's wait counts; see wait_vmcnt_le and a register fence).
-__device__ __forceinline__ uint32_t gload4(const void* p) {
-  uint32_t v;
-  asm volatile("global_load_dword %0, %1, off" : "=v"(v) : "v"(p) : "memory");
-  return v;
-}
-
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");

@@ -196,19 +196,6 @@ struct Ring {
   }
 };
 
-// 16-byte global load into VGPRs, issued from inline asm like the copies, so
-// that the compiler does not track it: the caller waits with an explicit
-// vmcnt and then fences the registers (vector-memory operations retire in
-// issue order, so the loads issued before the copies complete first).
-__device__ __forceinline__ u32x4 gload16(const void* p) {
-  u32x4 v;
-  asm volatile("global_load_dwordx4 %0, %1, off" : "=v"(v) : "v"(p) : "memory");
-  return v;
-}
-// Orders every later use of v after the preceding (volatile) wait.
-template <class V>
-__device__ __forceinline__ void reg_fence(V& v) { asm volatile("" : "+v"(v)); }
-
 template <int D, int QB, int WR, bool F8, bool PAGED, int NT = kThreads>
 __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   // F8: keys and values are OCP E4M3 codes (scaled per KV head), widened to
@@ -223,7 +210,7 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   constexpr int PARK_BYTES = PARK_O + (WK > 1 ? WR * WK * QB * 64 * 8 : 0);
   constexpr int SMEM = R::BYTES > PARK_BYTES ? R::BYTES : PARK_BYTES;
   static_assert(R::NS >= 2 * WK, "ring must hold two rounds");
-  static_assert(QB * DB + 2 + R::NS * R::DPS <= 63, "vector-memory counter range");
+  static_assert(R::NS * R::DPS <= 63, "vector-memory counter range");
   __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
 
   const int tid = threadIdx.x;
@@ -310,9 +297,7 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
                     (PAGED ? 0 : (static_cast<size_t>(b) * p.Hkv + g) * p.L_cap * D);
   const KV* vbase = static_cast<const KV*>(p.v) +
                     (PAGED ? 0 : (static_cast<size_t>(b) * p.Hkv + g) * p.L_cap * D);
-  // paged: the split's first 256 page ids, one per lane and register, loaded
-  // ahead of the query rows.  (Ordinary loads: the first copy's address needs
-  // them, so the compiler's wait, which covers the query rows too, costs nothing.)
+  // paged: the split's first 256 page ids, one per lane and register
   const int first_page = PAGED ? (start >> p.page_shift) : 0;
   uint32_t pg[4] = {0u, 0u, 0u, 0u};
   if constexpr (PAGED) {
@@ -326,8 +311,8 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   const bool wave_live = rowbase < m_live;  // padding waves only copy and sync
 
   // ---- query fragments straight to VGPRs (B operand of S^T = K Q^T): lane
-  //      holds Q[row l16][d = 32*db + 8*l4 .. +8]; issued before every copy
-  u32x4 qraw[QB][DB];
+  //      holds Q[row l16][d = 32*db + 8*l4 .. +8]
+  bf16x8 qf[QB][DB];
 #pragma unroll
   for (int qb = 0; qb < QB; ++qb) {
     const int r = min(rowbase + qb * 16 + l16, p.M - 1);
@@ -335,8 +320,14 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
     const uint16_t* src = static_cast<const uint16_t*>(p.q) +
                           ((static_cast<size_t>(b) * p.T + i) * p.Hq + g * p.G + hg) * D + 8 * l4;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) qraw[qb][db] = gload16(src + 32 * db);
+    for (int db = 0; db < DB; ++db) qf[qb][db] = *reinterpret_cast<const bf16x8*>(src + 32 * db);
   }
+  // ---- parent[] entries for deriving ancestor words in-kernel (trees of <= 128
+  //      nodes: two per lane)
+  const bool small_tree = p.W <= 2;
+  const int32_t* pb = p.parent + static_cast<size_t>(b) * p.T;
+  int par_lo = lane < p.T ? pb[lane] : -1;
+  int par_hi = lane + 64 < p.T ? pb[lane + 64] : -1;
   if constexpr (PAGED) {  // an id out of range is reported and page 0 read instead
     bool bad = false;
 #pragma unroll
@@ -348,6 +339,18 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
     }
     if (__any(bad) && tid == 0) ptd::report(p.dev_status, PTD_ERR_PAGE);
   }
+  // All of these loads are waited for here, ahead of the first copy: the compiler
+  // does not count the copies, so a wait that it places later would be for every
+  // copy in flight too.  (Loaded by inline asm like the copies, they needed no such
+  // wait, but the compiler takes the registers of such a load as written at once
+  // and may copy or reuse them while the data is on its way.  Ordinary loads cost
+  // up to 0.3 us a call on cold caches, 32 heads x 64 rows x 2112 keys 20.9 against
+  // 20.7, and 1-2 % of a batch's call on warm ones.)
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+    for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(qf[qb][db]));
+  asm volatile("" : "+v"(par_lo), "+v"(par_hi));
 
   // ---- sub-tile copies: thread tid moves chunks u*512 + tid of the
   //      sub-tile's 2*32*CH chunks (K rows, then V rows); chunk u of a thread
@@ -427,19 +430,6 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   const int ntiles = (end - start + R::SUB - 1) / R::SUB;
   const int nrounds = (ntiles + WK - 1) / WK;
   const int ninit = min(ntiles, R::NS);
-
-  // ---- parent[] entries for deriving ancestor words in-kernel (trees of
-  //      <= 128 nodes: two per lane), loaded untracked like the query rows
-  //      and, like them, before any copy
-  const bool small_tree = p.W <= 2;
-  // No branch and no default value around such a load: the compiler takes its
-  // register as written at once, so a merge with another value may copy it
-  // before the data is there.  Lanes past the tree read its last entry.
-  const int32_t* pb = p.parent + static_cast<size_t>(b) * p.T;
-  uint32_t par_raw0 = ptd::gload4(pb + min(lane, p.T - 1));
-  uint32_t par_raw1 = ptd::gload4(pb + min(lane + 64, p.T - 1));
-  int par_lo = -1, par_hi = -1;
-  bf16x8 qf[QB][DB];  // set from qraw once the first wait has covered the loads
 
   // per-lane LDS byte offsets inside a sub-tile (the row's swizzle is the
   // same for both 16-row halves, which therefore differ by a constant)
@@ -775,19 +765,8 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   };
 
   for (int t = 0; t < ninit; ++t) issue(t, t);
-  wait_vmcnt_le((ninit - min(ntiles, WK)) * R::DPS);  // round 0 (query rows, parents) landed
+  wait_vmcnt_le((ninit - min(ntiles, WK)) * R::DPS);  // round 0 landed
   lds_barrier();
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      reg_fence(qraw[qb][db]);
-      qf[qb][db] = __builtin_bit_cast(bf16x8, qraw[qb][db]);
-    }
-  reg_fence(par_raw0);
-  reg_fence(par_raw1);
-  par_lo = lane < p.T ? static_cast<int>(par_raw0) : -1;
-  par_hi = lane + 64 < p.T ? static_cast<int>(par_raw1) : -1;
 
   // rounds whose wait count is the steady-state constant: every refill so far
   // issued in full (R::NS + (rd - 1) * WK <= ntiles)
