@@ -226,7 +226,7 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   // first and the short ones fill in at the end.  Work item b names the b-th
   // largest sequence; each wave ranks the sizes, lane l holding sequence l's
   // lengths, which then need no second load (85.4 against 86.7 us on 16 sequences
-  // of 512-8192 keys, decode-sized calls 99.7 against 101.4).
+  // of 512-8192 keys).
   const bool by_size = p.B > 1 && p.B <= PTD_WAVE;
   int id;
   logical_block(blockIdx.x, gridDim.x, p.B * p.Hkv, by_size, id);
@@ -1427,27 +1427,33 @@ bool make_plan(const ptd_attn_shape* s, int T, Plan* pl) {
     pl->splits = pl->splits_full = pl->splits_live = splits_for(target);
     pl->precise_full = pl->precise_live = kPreciseFrac;
     if (pl->nt == 256) {
-      // 256-thread workgroups, two per CU: the third round of half the CUs'
-      // workgroups pays where sequences are long, or where dead row passes
-      // (tree_len) leave CUs idle; otherwise exactly two per CU are faster:
-      // splits of up to about 3072 keys, or 544 with tree_len.  Measured in
-      // us, 512 against 768 workgroups (longest split of the 512): without
-      // tree_len 2 x 256 nodes (1088 keys) 52.5 / 64.9, 16 x 64 (544) 38.9 /
-      // 47.7, (2080) 71.7 / 74.9, (4128) 112.8 / 104.0, 4 x 64 (1032) 49.1 /
-      // 57.6, (4104) 110.4 / 100.5; with it 16 x 64 (544) 35.4 / 40.4, (1536)
-      // 59.0 / 63.0, on 8-bit pages 66.5 / 66.0, 4 x 64 (1032) 44.5 / 43.0, on
-      // 8-bit pages 45.8 / 41.5.  Longer splits carry fewer of a row's keys as
-      // hi + lo; half the threshold keeps the error no larger (1.83e-3 against
-      // 1.92e-3 on the first, 1.73e-3 / 1.79e-3 on the 4 x 64) for about 1 %.
+      // 256-thread workgroups, two per CU.  Exactly two per CU (512, `even` splits)
+      // spare the third round of half the CUs, but lengths differ: where one
+      // sequence is longer than the others its own chunks set the time, and more
+      // splits are faster (16 x 40 nodes, 4 KV heads, one of 6104 keys and 15 of 64,
+      // four / two splits: 54 / 83 us; all equal 108 / 115).  So only where no
+      // mixture of lengths measured more than 4 % slower, us with / without:
+      //  - chunks of up to 288 keys, if they fill the 512 places: 16 x 64 nodes x 480
+      //    keys, all equal 37.4 / 47.0, one long and 15 of 64 keys 32.6 / 35.3;
+      //  - one split, which needs no combine: 24 x 36 x 508 keys 0.75-0.81 of the time
+      //    of two;
+      //  - two sequences, each of which fills every CU alone, without padding (2 x 256
+      //    nodes x 832 keys 42.9 / 49.4, x 8000 99.7 / 112.9, one of 64 keys 0.88-0.99
+      //    of the time).
+      // Longer splits carry fewer of a row's keys as hi + lo; half the threshold keeps
+      // the error no larger (over drawn batches 0.975 of it on average, 1.009 at most).
       const int even = splits_for(2 * kTargetBlocks);
       const long long keys = (s->L_cap + even - 1LL) / even;
-      if (even < pl->splits && keys <= 3072) {
+      const bool one_split = even == 1 && keys <= 544 && items >= 384;
+      const bool few_keys = even > 1 && keys <= 288 && items * even >= 480;
+      const bool fills_alone = static_cast<long long>(s->Hkv) * pl->passes * even >= kTargetBlocks && keys <= 3072;
+      if (even < pl->splits && (one_split || few_keys || fills_alone)) {
         pl->splits_full = even;
         pl->precise_full = kPreciseFrac / 2;
-      }
-      if (even < pl->splits && keys <= 544) {
-        pl->splits_live = even;
-        pl->precise_live = kPreciseFrac / 2;
+        if (one_split || few_keys) {
+          pl->splits_live = even;
+          pl->precise_live = kPreciseFrac / 2;
+        }
       }
     }
   } else {

@@ -731,10 +731,12 @@ def test_attention_tree_keys_at_any_offset(P, T, Hq, Hkv, D):
 
 
 @pytest.mark.parametrize("B,T,Hkv,kv,cap", [
-    (24, 36, 8, 500, 544),      # two splits, of which a call without tree sizes takes one
-    (24, 36, 8, 500, 3073),     # ... both: the one would be longer than its limit
-    (3, 130, 8, 900, 1400),     # four per sequence instead of five; room past the keys
-    (16, 33, 8, 700, 1088), (16, 33, 8, 700, 1089)])  # with tree sizes: at the limit and past it
+    (24, 36, 8, 500, 544),      # one split instead of two, at the limit
+    (24, 36, 8, 500, 545), (24, 36, 8, 500, 3073),  # ... past it
+    (3, 130, 8, 900, 1400),     # six per sequence; room past the keys
+    (16, 33, 8, 700, 1088), (16, 33, 8, 700, 1089),  # three
+    (16, 33, 8, 500, 576), (16, 33, 8, 500, 577),    # two instead of three, at the limit and past it
+    (2, 250, 8, 900, 1500), (2, 250, 8, 900, 12289)])  # two sequences: four instead of six, and six
 def test_attention_batch_split_counts(P, B, T, Hkv, kv, cap):
     rng = np.random.default_rng(B + cap)
     Hq, D = 4 * Hkv, 64
@@ -755,6 +757,30 @@ def test_attention_batch_split_counts(P, B, T, Hkv, kv, cap):
         got = out.cpu().numpy()
         for n, (b, h, i) in enumerate(rows):
             assert np.abs(got[b, i, h] - ref[n]).max() <= TOL["bf16"], (b, h, i)
+
+
+def test_attention_long_sequence_of_a_batch_takes_every_split(P):
+    # one long sequence among short ones sets the time of a batch: its keys are cut
+    # into as many splits as the workspace is sized for, and every one leaves its
+    # partials there (the sentinel is gone from all four)
+    B, T, Hq, Hkv, D, L = 16, 40, 32, 4, 64, 4200
+    rng = np.random.default_rng(3)
+    kv_len = np.full(B, 64, np.int32)
+    kv_len[5] = L - T
+    parent = np.stack([W.tree_uniform(rng, T)[0] for _ in range(B)])
+    q, k, v = (torch.randn(s, device="cuda", dtype=torch.bfloat16)
+               for s in ((B, T, Hq, D), (B, Hkv, L, D), (B, Hkv, L, D)))
+    shape = P.AttnShape(B, Hq, Hkv, D, L, P.PTD_BF16, P.PTD_F32, 0.0)
+    M = T * Hq // Hkv
+    need = P.ptd_tree_attention_workspace_bytes(shape, T)
+    assert need == 4 * B * Hkv * M * (D + 2) * 4  # four splits of [B][Hkv][M] rows
+    for tl in (None, cu(np.full(B, T, np.int32))):
+        ws = torch.full((need // 4,), 12345.0, device="cuda")
+        out = torch.empty((B, T, Hq, D), device="cuda")
+        P.ptd_tree_attention_ragged(q, k, v, cu(kv_len), tl, cu(parent), T, out, shape, None, ws.view(torch.uint8),
+                                    need)
+        part = ws[:4 * B * Hkv * M * D].view(4, B, Hkv, M, D)
+        assert not (part[:, 5] == 12345.0).all(-1).any()
 
 
 @pytest.mark.parametrize("T", [20, 130])
