@@ -210,6 +210,10 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   constexpr int PARK_BYTES = PARK_O + (WK > 1 ? WR * WK * QB * 64 * 8 : 0);
   constexpr int SMEM = R::BYTES > PARK_BYTES ? R::BYTES : PARK_BYTES;
   static_assert(R::NS >= 2 * WK, "ring must hold two rounds");
+  constexpr int QROWS = 16 * QB * WR;             // query rows of a workgroup
+  constexpr int CHQ = D / 8;                      // 16-byte chunks of one
+  constexpr int QS = (QROWS * D * 2 + R::SLOT - 1) / R::SLOT;  // ring slots that hold them at first
+  static_assert(R::NS - QS >= WK, "round 0 beside the query rows");
   static_assert(R::NS * R::DPS <= 63, "vector-memory counter range");
   __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
 
@@ -310,18 +314,6 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   const int rowbase = pr0 + wr * 16 * QB;
   const bool wave_live = rowbase < m_live;  // padding waves only copy and sync
 
-  // ---- query fragments straight to VGPRs (B operand of S^T = K Q^T): lane
-  //      holds Q[row l16][d = 32*db + 8*l4 .. +8]
-  bf16x8 qf[QB][DB];
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const int r = min(rowbase + qb * 16 + l16, p.M - 1);
-    const int i = r / p.G, hg = r % p.G;
-    const uint16_t* src = static_cast<const uint16_t*>(p.q) +
-                          ((static_cast<size_t>(b) * p.T + i) * p.Hq + g * p.G + hg) * D + 8 * l4;
-#pragma unroll
-    for (int db = 0; db < DB; ++db) qf[qb][db] = *reinterpret_cast<const bf16x8*>(src + 32 * db);
-  }
   // ---- parent[] entries for deriving ancestor words in-kernel (trees of <= 128
   //      nodes: two per lane)
   const bool small_tree = p.W <= 2;
@@ -339,23 +331,41 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
     }
     if (__any(bad) && tid == 0) ptd::report(p.dev_status, PTD_ERR_PAGE);
   }
-  // All of these loads are waited for here, ahead of the first copy: the compiler
-  // does not count the copies, so a wait that it places later would be for every
-  // copy in flight too.  (Loaded by inline asm like the copies, they needed no such
-  // wait, but the compiler takes the registers of such a load as written at once
-  // and may copy or reuse them while the data is on its way.  Ordinary loads cost
-  // up to 0.3 us a call on cold caches, 32 heads x 64 rows x 2112 keys 20.9 against
-  // 20.7, and 1-2 % of a batch's call on warm ones.)
-#pragma unroll
-  for (int qb = 0; qb < QB; ++qb)
-#pragma unroll
-    for (int db = 0; db < DB; ++db) asm volatile("" : "+v"(qf[qb][db]));
-  asm volatile("" : "+v"(par_lo), "+v"(par_hi));
-
   // ---- sub-tile copies: thread tid moves chunks u*512 + tid of the
   //      sub-tile's 2*32*CH chunks (K rows, then V rows); chunk u of a thread
   //      is K or V for the whole wave (SUB*CH is a multiple of 64)
   const uint32_t ring = lds_addr(smem);
+  // ---- query rows to the ring's last slots, ahead of the first sub-tiles; their
+  //      fragments are read once both have landed, then the slots get theirs.
+  //      Row r's chunk s lies at position s ^ (r mod CHQ).  (Loads into registers
+  //      have to be waited for before the first copy, as the compiler does not count
+  //      the copies: 32 heads x 64 rows x 2112 keys with the embedding 20.9 against
+  //      20.5 us, batches 0.2-0.5 us a call.  From inline asm, fenced after a later
+  //      wait, the compiler takes their registers as written at once and may copy or
+  //      reuse them while the data is on its way.)
+  {
+    constexpr int STEP = NT / CHQ;  // rows per copy (a multiple of CHQ)
+    const int row = tid / CHQ;
+    const int ch = (tid % CHQ) ^ (row & (CHQ - 1));
+    int r = pr0 + row, i = r / p.G, hg = r % p.G;
+    const int di = STEP / p.G, dh = STEP % p.G;  // uniform
+    const uint16_t* qb0 = static_cast<const uint16_t*>(p.q) +
+                          (static_cast<size_t>(b) * p.T * p.Hq + g * p.G) * D + 8 * ch;
+#pragma unroll
+    for (int u = 0; u < (QROWS + STEP - 1) / STEP; ++u) {
+      if (u * STEP + wave * PTD_WAVE / CHQ < QROWS) {  // uniform; rows past the last one re-read it
+        const int ic = r < p.M ? i : p.T - 1, hc = r < p.M ? hg : p.G - 1;
+        dma16(qb0 + (static_cast<size_t>(ic) * p.Hq + hc) * D, ring + (R::NS - QS) * R::SLOT + (u * NT + wave * PTD_WAVE) * 16);
+      }
+      r += STEP;
+      i += di;
+      hg += dh;
+      if (hg >= p.G) {
+        hg -= p.G;
+        ++i;
+      }
+    }
+  }
   uint32_t cp_voff[R::DPS], cp_lds[R::DPS];
   int cp_row[R::DPS], cp_off[R::DPS];
   bool cp_v[R::DPS];
@@ -430,6 +440,10 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
   const int ntiles = (end - start + R::SUB - 1) / R::SUB;
   const int nrounds = (ntiles + WK - 1) / WK;
   const int ninit = min(ntiles, R::NS);
+
+  // query fragments (B operand of S^T = K Q^T: lane holds Q[row l16][d = 32*db +
+  // 8*l4 .. +8]), read once they have landed
+  bf16x8 qf[QB][DB];
 
   // per-lane LDS byte offsets inside a sub-tile (the row's swizzle is the
   // same for both 16-row halves, which therefore differ by a constant)
@@ -764,9 +778,21 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
     return pmask;
   };
 
-  for (int t = 0; t < ninit; ++t) issue(t, t);
-  wait_vmcnt_le((ninit - min(ntiles, WK)) * R::DPS);  // round 0 landed
+  const int nfirst = min(ninit, R::NS - QS);
+  for (int t = 0; t < nfirst; ++t) issue(t, t);
+  wait_vmcnt_le((nfirst - min(ntiles, WK)) * R::DPS);  // query rows and round 0 landed
   lds_barrier();
+#pragma unroll
+  for (int qb = 0; qb < QB; ++qb)
+#pragma unroll
+    for (int db = 0; db < DB; ++db)
+      qf[qb][db] = *reinterpret_cast<const bf16x8*>(
+          smem + (R::NS - QS) * R::SLOT + ((wr * QB + qb) * 16 + l16) * D * 2 +
+          ((db * 4 + l4) ^ (l16 & (CHQ - 1))) * 16);
+  if (ninit > nfirst) {  // uniform
+    lds_barrier();  // every wave has its fragments
+    for (int t = nfirst; t < ninit; ++t) issue(t, t);
+  }
 
   // rounds whose wait count is the steady-state constant: every refill so far
   // issued in full (R::NS + (rd - 1) * WK <= ntiles)
