@@ -759,6 +759,42 @@ def test_attention_batch_split_counts(P, B, T, Hkv, kv, cap):
             assert np.abs(got[b, i, h] - ref[n]).max() <= TOL["bf16"], (b, h, i)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("B,T,G,Hkv", [(1, 16, 1, 256), (1, 96, 1, 128), (1, 64, 4, 128), (2, 47, 4, 128)])
+def test_attention_first_subtiles_beside_the_query_rows(P, B, T, G, Hkv, D):
+    # the four plans without KV splits: as many 32-key sub-tiles as fit the ring
+    # beside the query rows, one and more above, the whole ring, one above; a last
+    # sub-tile of one key.  Against fp64; E4M3 caches give the same bits
+    L, dev = 15 * 32, "cuda"
+    g = torch.Generator(device=dev).manual_seed(T + D)
+    q = torch.randn((B, T, G * Hkv, D), generator=g, device=dev, dtype=torch.bfloat16)
+    codes = [torch.randn((B, Hkv, L, D), generator=g, device=dev).to(torch.float8_e4m3fn) for _ in range(2)]
+    k, v = (c.to(torch.bfloat16) for c in codes)
+    par = W.tree_uniform(np.random.default_rng(T), T)[0]
+    anc = np.eye(T, dtype=bool)
+    for i in range(T):
+        if par[i] >= 0:
+            anc[i] |= anc[par[i]]
+    parent = cu(np.stack([par] * B).astype(np.int32))
+    for N in [32 * n + e for n in range(1, 14) for e in (-31, 0) if 32 * n + e >= T]:
+        kv_len = torch.full((B,), N - T, dtype=torch.int32, device=dev)
+        st = status_buf()
+        out = P.tree_attention(q, k, v, kv_len, parent, out_dtype=torch.float32, dev_status=st)
+        assert st.item() == 0
+        vis = torch.ones((T, N), dtype=torch.bool, device=dev)
+        vis[:, N - T:] = cu(anc)
+        qq = q.double().view(B, T, Hkv, G, D).permute(0, 2, 1, 3, 4).reshape(B, Hkv, T * G, D)
+        sc = torch.matmul(qq, k[:, :, :N].double().transpose(2, 3).contiguous()) / D ** 0.5
+        sc = sc.view(B, Hkv, T, G, N).masked_fill(~vis[:, None], -torch.inf).view(B, Hkv, T * G, N)
+        ref = torch.matmul(torch.softmax(sc, -1), v[:, :, :N].double())
+        ref = ref.view(B, Hkv, T, G, D).permute(0, 2, 1, 3, 4).reshape(B, T, Hkv * G, D)
+        assert (out.double() - ref).abs().max().item() <= TOL["bf16"], N
+        if D == 128:
+            out8 = P.tree_attention_fp8kv(q, codes[0].view(torch.uint8), codes[1].view(torch.uint8), None, None,
+                                          kv_len, parent, out_dtype=torch.float32, dev_status=st)
+            assert st.item() == 0 and torch.equal(out8, out), N
+
+
 def test_attention_long_sequence_of_a_batch_takes_every_split(P):
     # one long sequence among short ones sets the time of a batch: its keys are cut
     # into as many splits as the workspace is sized for, and every one leaves its
