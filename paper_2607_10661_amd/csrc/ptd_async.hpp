@@ -80,21 +80,6 @@ __device__ __forceinline__ void dma16_s2(const void* base0, uint32_t voff0, uint
       : "memory");
 }
 
-// Same, 4 bytes per lane (lane l lands at lds + 4*l).
-__device__ __forceinline__ void dma4(const void* gptr, uint32_t lds) {
-  lds = uniform_u32(lds);
-  uint32_t saved;
-  asm volatile(
-      "s_mov_b32 %0, m0\n\t"
-      "s_mov_b32 m0, %1\n\t"
-      "s_nop 0\n\t"
-      "global_load_lds_dword %2, off\n\t"
-      "s_mov_b32 m0, %0"
-      : "=&s"(saved)
-      : "s"(lds), "v"(gptr)
-      : "memory");
-}
-
 template <int N>
 __device__ __forceinline__ void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");

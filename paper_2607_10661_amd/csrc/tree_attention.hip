@@ -39,7 +39,6 @@ namespace {
 
 using ptd::dma16;
 using ptd::dma16_s;
-using ptd::dma4;
 using ptd::lds_addr;
 using ptd::lds_barrier;
 using ptd::wait_vmcnt;
@@ -331,9 +330,7 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
     }
     if (__any(bad) && tid == 0) ptd::report(p.dev_status, PTD_ERR_PAGE);
   }
-  // ---- sub-tile copies: thread tid moves chunks u*512 + tid of the
-  //      sub-tile's 2*32*CH chunks (K rows, then V rows); chunk u of a thread
-  //      is K or V for the whole wave (SUB*CH is a multiple of 64)
+
   const uint32_t ring = lds_addr(smem);
   // ---- query rows to the ring's last slots, ahead of the first sub-tiles; their
   //      fragments are read once both have landed, then the slots get theirs.
@@ -355,7 +352,8 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
     for (int u = 0; u < (QROWS + STEP - 1) / STEP; ++u) {
       if (u * STEP + wave * PTD_WAVE / CHQ < QROWS) {  // uniform; rows past the last one re-read it
         const int ic = r < p.M ? i : p.T - 1, hc = r < p.M ? hg : p.G - 1;
-        dma16(qb0 + (static_cast<size_t>(ic) * p.Hq + hc) * D, ring + (R::NS - QS) * R::SLOT + (u * NT + wave * PTD_WAVE) * 16);
+        dma16(qb0 + (static_cast<size_t>(ic) * p.Hq + hc) * D,
+              ring + (R::NS - QS) * R::SLOT + (u * NT + wave * PTD_WAVE) * 16);
       }
       r += STEP;
       i += di;
@@ -366,6 +364,10 @@ __global__ void __launch_bounds__(NT, kThreads / NT) k_attn_mfma(AttnParams p) {
       }
     }
   }
+
+  // ---- sub-tile copies: thread tid moves chunks u*512 + tid of the
+  //      sub-tile's 2*32*CH chunks (K rows, then V rows); chunk u of a thread
+  //      is K or V for the whole wave (SUB*CH is a multiple of 64)
   uint32_t cp_voff[R::DPS], cp_lds[R::DPS];
   int cp_row[R::DPS], cp_off[R::DPS];
   bool cp_v[R::DPS];
@@ -1458,7 +1460,7 @@ bool make_plan(const ptd_attn_shape* s, int T, Plan* pl) {
       // sequence is longer than the others its own chunks set the time, and more
       // splits are faster (16 x 40 nodes, 4 KV heads, one of 6104 keys and 15 of 64,
       // four / two splits: 54 / 83 us; all equal 108 / 115).  So only where no
-      // mixture of lengths measured more than 4 % slower, us with / without:
+      // mixture of lengths measured more than 5 % slower, us with / without:
       //  - chunks of up to 288 keys, if they fill the 512 places: 16 x 64 nodes x 480
       //    keys, all equal 37.4 / 47.0, one long and 15 of 64 keys 32.6 / 35.3;
       //  - one split, which needs no combine: 24 x 36 x 508 keys 0.75-0.81 of the time
