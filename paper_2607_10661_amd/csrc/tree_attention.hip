@@ -1464,18 +1464,23 @@ bool make_plan(const ptd_attn_shape* s, int T, Plan* pl) {
       //  - chunks of up to 288 keys, if they fill the 512 places: 16 x 64 nodes x 480
       //    keys, all equal 37.4 / 47.0, one long and 15 of 64 keys 32.6 / 35.3;
       //  - one split, which needs no combine: 24 x 36 x 508 keys 0.75-0.81 of the time
-      //    of two;
-      //  - two sequences, each of which fills every CU alone, without padding (2 x 256
-      //    nodes x 832 keys 42.9 / 49.4, x 8000 99.7 / 112.9, one of 64 keys 0.88-0.99
-      //    of the time).
+      //    of two; up to 704 keys without padding;
+      //  - two sequences, each of which has a workgroup for 7/8 of the CUs alone,
+      //    without padding (2 x 256 nodes x 832 keys 42.9 / 49.4, x 8000 99.7 / 112.9,
+      //    2 x 211 nodes of 585-1171 keys 33.0 / 41.5; one of 64 keys 0.88-1.05 of the
+      //    time), chunks of up to 1024 keys where the splits are more than 1.5 times
+      //    fewer (0.86 of the time on average, one of 64 keys 0.95, at worst 1.10; from
+      //    there on up to 1.12).
       // Longer splits carry fewer of a row's keys as hi + lo; half the threshold keeps
       // the error no larger (over drawn batches 0.975 of it on average, 1.009 at most).
       const int even = splits_for(2 * kTargetBlocks);
       const long long keys = (s->L_cap + even - 1LL) / even;
       const bool one_split = even == 1 && keys <= 544 && items >= 384;
+      const bool one_short = even == 1 && keys <= 704;
       const bool few_keys = even > 1 && keys <= 288 && items * even >= 480;
-      const bool fills_alone = static_cast<long long>(s->Hkv) * pl->passes * even >= kTargetBlocks && keys <= 3072;
-      if (even < pl->splits && (one_split || few_keys || fills_alone)) {
+      const bool fills_alone = static_cast<long long>(s->Hkv) * pl->passes * even >= kTargetBlocks * 7 / 8 &&
+                               keys <= (2 * pl->splits <= 3 * even ? 3072 : 1024);
+      if (even < pl->splits && (one_split || one_short || few_keys || fills_alone)) {
         pl->splits_full = even;
         pl->precise_full = kPreciseFrac / 2;
         if (one_split || few_keys) {
