@@ -1459,10 +1459,13 @@ bool make_plan(const ptd_attn_shape* s, int T, Plan* pl) {
       // spare the third round of half the CUs, but lengths differ: where one
       // sequence is longer than the others its own chunks set the time, and more
       // splits are faster (16 x 40 nodes, 4 KV heads, one of 6104 keys and 15 of 64,
-      // four / two splits: 54 / 83 us; all equal 108 / 115).  So only where no
-      // mixture of lengths measured more than 5 % slower, us with / without:
-      //  - chunks of up to 288 keys, if they fill the 512 places: 16 x 64 nodes x 480
-      //    keys, all equal 37.4 / 47.0, one long and 15 of 64 keys 32.6 / 35.3;
+      // four / two splits: 54 / 83 us; all equal 108 / 115).  So only where the chunks
+      // are short or a sequence fills the CUs alone, us with / without:
+      //  - chunks of up to 512 keys without padding: over 613 drawn batches 0.87 of the
+      //    time (at worst 1.07), one long among ones of 1/2 to 1/16 0.93 (1.21), among
+      //    ones of 64 keys 1.00 (1.25); chunks of up to 640 keys 1.08 there (1.33);
+      //  - of up to 288 keys with it, if they fill the 512 places (0.97, 0.99, 1.01): 16
+      //    x 64 nodes x 480 keys 37.4 / 47.0, one long and 15 of 64 keys 32.6 / 35.3;
       //  - one split, which needs no combine: 24 x 36 x 508 keys 0.75-0.81 of the time
       //    of two; up to 704 keys without padding;
       //  - two sequences, each of which has a workgroup for 7/8 of the CUs alone,
@@ -1478,9 +1481,10 @@ bool make_plan(const ptd_attn_shape* s, int T, Plan* pl) {
       const bool one_split = even == 1 && keys <= 544 && items >= 384;
       const bool one_short = even == 1 && keys <= 704;
       const bool few_keys = even > 1 && keys <= 288 && items * even >= 480;
+      const bool few_short = even > 1 && keys <= 512 && items * even >= 400;
       const bool fills_alone = static_cast<long long>(s->Hkv) * pl->passes * even >= kTargetBlocks * 7 / 8 &&
                                keys <= (2 * pl->splits <= 3 * even ? 3072 : 1024);
-      if (even < pl->splits && (one_split || one_short || few_keys || fills_alone)) {
+      if (even < pl->splits && (one_split || one_short || few_keys || few_short || fills_alone)) {
         pl->splits_full = even;
         pl->precise_full = kPreciseFrac / 2;
         if (one_split || few_keys) {

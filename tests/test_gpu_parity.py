@@ -734,8 +734,8 @@ def test_attention_tree_keys_at_any_offset(P, T, Hq, Hkv, D):
     (24, 36, 8, 500, 544), (24, 36, 8, 500, 545),    # one split instead of two, at the limit with tree sizes
     (24, 36, 8, 500, 704), (24, 36, 8, 500, 705),    # ... and without, past it
     (3, 130, 8, 900, 1400),     # six per sequence; room past the keys
-    (16, 33, 8, 700, 1088), (16, 33, 8, 700, 1089),  # three
-    (16, 33, 8, 500, 576), (16, 33, 8, 500, 577),    # two instead of three, at the limit and past it
+    (16, 33, 8, 500, 576), (16, 33, 8, 500, 577),    # two instead of three, at the limit with tree sizes
+    (16, 33, 8, 700, 1024), (16, 33, 8, 700, 1025),  # ... and without, past it
     (2, 250, 8, 900, 1500), (2, 250, 8, 900, 12289), # two sequences: four instead of six, and six
     (2, 220, 8, 900, 1500), (2, 70, 8, 900, 10240), (2, 70, 8, 900, 10241)])  # ten instead of sixteen, at the limit
 def test_attention_batch_split_counts(P, B, T, Hkv, kv, cap):
